@@ -34,14 +34,15 @@
 // its eight output rows once. No global read is waited for in line with the
 // layers. The last conv layer is pooled straight from the accumulators.
 //
-// Training: the forward also stores a1..a4 (BF16) and the pooled features;
-// the head backward runs per patch in FP32; the conv backward walks layers
-// 4 -> 1 per patch with two LDS buffers (layer input and gradient), computing
+// Training: the forward also stores a1..a3 (BF16), the signs of a4 and the
+// pooled features; one kernel then takes each patch through the head's
+// backward (FP32) and the conv layers 4 -> 1 with two LDS buffers (layer input
+// and gradient), computing
 //   dW[tap][ci][co] += sum_p X[p + tap][ci] dZ[p][co]        (MFMA, K = pixels)
 //   dX[p][ci] = sum_tap,co dZ[p - tap][co] W[tap][ci][co]   (MFMA, K = channels)
-// Weight gradients accumulate in FP32 registers per workgroup over its
-// patches and are summed over workgroups in a fixed order, so results do not
-// depend on scheduling.
+// Weight gradients accumulate in FP32 per workgroup over its patches and are
+// summed over workgroups in a fixed order (together with the Adam update in a
+// training step), so results do not depend on scheduling.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -379,7 +380,9 @@ struct FwdArgs {
     float *pred;            // [B][2] log kxx, log kyy
     float *stats;           // [B][8] mean, std, lag-1 corr x, y, the 4 features (or null)
     float *spread;          // [B][2] max - min over the n_sym predictions (or null)
-    __bf16 *acts;           // [4][B][1024][32] when training, else null
+    __bf16 *acts;           // [3][B][1024][32] a1..a3 when training, else null
+    unsigned *mask4;        // [B][1024] when training: bit 8 k + 4 ct + j of a pixel's word is a4 > 0 of
+                            // its channel 16 ct + 4 k + j (all that the backward pass needs of a4)
     float *pool_out;        // [B][37] head input when training
     int *next;              // patches claimed beyond the first gridDim.x (zeroed by k_pack)
 };
@@ -509,6 +512,7 @@ __device__ __forceinline__ void conv_body(const __bf16 *__restrict__ in_p, __bf1
     auto epilogue = [&](int k, const f32x4 (&ac)[2]) {
         const int y = r0 + k;
         const int p = y * kSide + col0;  // D column = pixel
+        unsigned bits = 0;
 #pragma unroll
         for (int ct = 0; ct < 2; ++ct) {
             bf16x4 v;
@@ -525,8 +529,14 @@ __device__ __forceinline__ void conv_body(const __bf16 *__restrict__ in_p, __bf1
                 if (k == kRows - 1 && r0 == kSide - kRows)
                     *reinterpret_cast<lds_bf16x4 *>(obase + (k - kSide) * kActRow + op[ct]) = v;
             }
-            if (GOUT) *reinterpret_cast<glb_bf16x4 *>(gout + p * kC + ct * 16 + g * 4) = v;
+            if (GOUT && !POOL) *reinterpret_cast<glb_bf16x4 *>(gout + p * kC + ct * 16 + g * 4) = v;
+            if (GOUT && POOL) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) bits |= ((float)v[i] > 0.0f ? 1u : 0u) << (4 * ct + i);
+            }
         }
+        // the last layer's activations go out as one sign bit each
+        if (GOUT && POOL) ((__attribute__((address_space(1))) unsigned char *)gout_p)[4 * p + g] = (unsigned char)bits;
     };
     bf16x8 x[2][3];  // the operands of input rows i and i + 1
 #pragma unroll
@@ -699,7 +709,7 @@ __global__ __launch_bounds__(kT) void k_forward(FwdArgs a)
             // ---- conv2..conv4 on MFMA ----
             __bf16 *g2 = TRAIN ? a.acts + ((size_t)1 * a.batch + b) * kPix * kC : nullptr;
             __bf16 *g3 = TRAIN ? a.acts + ((size_t)2 * a.batch + b) * kPix * kC : nullptr;
-            __bf16 *g4 = TRAIN ? a.acts + ((size_t)3 * a.batch + b) * kPix * kC : nullptr;
+            unsigned *g4 = TRAIN ? a.mask4 + (size_t)b * kPix : nullptr;
             conv_mfma<false, true, TRAIN>(bufA, bufB, wbuf, a.wf + 9 * kC * kC, prm + oB2, g2, pool_part, pf, sn,
                                           xs);
             __syncthreads();
@@ -707,7 +717,8 @@ __global__ __launch_bounds__(kT) void k_forward(FwdArgs a)
                                            nullptr, 0, nullptr);
             __syncthreads();
             // stages conv2's weights for the next pass
-            conv_mfma<true, false, TRAIN>(bufA, nullptr, wbuf, a.wf, prm + oB4, g4, pool_part, nullptr, 0, nullptr);
+            conv_mfma<true, false, TRAIN>(bufA, nullptr, wbuf, a.wf, prm + oB4, reinterpret_cast<__bf16 *>(g4),
+                                          pool_part, nullptr, 0, nullptr);
             __syncthreads();
             // ---- pooling and head (FP32) ----
             if (tid < kC) {
@@ -809,280 +820,471 @@ __global__ __launch_bounds__(kT) void k_stats(const float *__restrict__ logk, in
     }
 }
 
-// Head backward per patch (one wave per patch), FP32. Loss L = mean over the
-// batch and both outputs of (prediction - target)^2. Writes the patch's head
-// gradient, dL/dpool and its loss term.
-__global__ __launch_bounds__(64) void k_head_backward(const float *__restrict__ prm,
-                                                      const float *__restrict__ pool, const float *__restrict__ target,
-                                                      const int8_t *__restrict__ sym, int batch,
-                                                      float *__restrict__ ghead, float *__restrict__ dpool,
-                                                      float *__restrict__ loss_terms)
-{
-    const int b = blockIdx.x, j = threadIdx.x;
-    if (b >= batch) return;
-    __shared__ float z[kZ], dh[kH], hh[kH];
-    __shared__ float dyv[2];
-    if (j < kZ) z[j] = pool[(size_t)b * kZ + j];
-    __syncthreads();
-    float hpre = 0.0f, h = 0.0f;
-    if (j < kH) {
-        hpre = prm[oC1 + j];
-        for (int k = 0; k < kZ; ++k) hpre += prm[oM1 + j * kZ + k] * z[k];
-        h = fmaxf(hpre, 0.0f);
-        hh[j] = h;
-    }
-    float y0 = j < kH ? prm[oM2 + j] * h : 0.0f, y1 = j < kH ? prm[oM2 + kH + j] * h : 0.0f;
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-        y0 += __shfl_xor(y0, off, 64);
-        y1 += __shfl_xor(y1, off, 64);
-    }
-    const float m = z[kC];
-    // a transposed patch is trained on the exchanged targets
-    const int tr = (sym && (sym[b] & 1)) ? 1 : 0;
-    const float e0 = y0 + prm[oC2] + m - target[2 * (size_t)b + tr];
-    const float e1 = y1 + prm[oC2 + 1] + m - target[2 * (size_t)b + 1 - tr];
-    const float scale = 2.0f / (2.0f * batch);
-    if (j == 0) {
-        dyv[0] = scale * e0;
-        dyv[1] = scale * e1;
-        loss_terms[b] = (e0 * e0 + e1 * e1) / (2.0f * batch);
-    }
-    __syncthreads();
-    float *g = ghead + (size_t)b * kNHead;  // same order as the parameters from oM1
-    if (j < kH) {
-        g[(oM2 - oM1) + j] = dyv[0] * hh[j];
-        g[(oM2 - oM1) + kH + j] = dyv[1] * hh[j];
-        const float d = (hpre > 0.0f) ? (dyv[0] * prm[oM2 + j] + dyv[1] * prm[oM2 + kH + j]) : 0.0f;
-        dh[j] = d;
-        g[(oC1 - oM1) + j] = d;
-        for (int k = 0; k < kZ; ++k) g[j * kZ + k] = d * z[k];
-    }
-    if (j < 2) g[(oC2 - oM1) + j] = dyv[j];
-    __syncthreads();
-    if (j < kC) {
-        float s = 0.0f;
-        for (int k = 0; k < kH; ++k) s += dh[k] * prm[oM1 + k * kZ + j];
-        dpool[(size_t)b * kC + j] = s;
-    }
-}
-
+// Weight gradients and input gradients of a batch, one workgroup per patch at
+// a time (256 workgroups, patches blockIdx, blockIdx + grid, ...).
 struct BwdArgs {
     const float *prm;
     const __bf16 *wb;      // [3][9][ci][co]
     const float *logk;     // [B][1024]
     const int8_t *sym;     // [B] or null
-    const __bf16 *acts;    // [4][B][1024][32]
-    const float *dpool;    // [B][32]
+    const __bf16 *acts;    // [3][B][1024][32]
+    const unsigned *mask4; // [B][1024] the sign bits of a4 (FwdArgs::mask4)
+    const float *pool;     // [B][37] head input
+    const float *target;   // [B][2]
     int batch;
-    float *gpart;          // [gridDim.x][kNConv] per-workgroup partial conv gradients
+    float *gpart;          // [gridDim.x][kGPart] per-workgroup sums of the gradients, then of the loss terms
 };
 
-// dW for one 32 -> 32 layer: wave w owns tile-jobs j = w, w + 8, ... of the
-// 36 (tap, co-tile, ci-tile) jobs; each job is a 16 x 16 block of dW[tap]
-// accumulated over the 1024 pixels (K) with D[m = co][n = ci].
-__device__ __forceinline__ void dw_mfma(const __bf16 *__restrict__ X, const __bf16 *__restrict__ dZ, f32x4 acc[5])
+// Sixteen channels of 8 consecutive pixels as an MFMA operand with pixels as
+// K: lane (n, g) gets channel n of pixels 8 g .. 8 g + 7 of a row stored
+// [pixel][channel]. A transposing read gives each lane four pixels of its
+// channel: within a group of 16 lanes, lane l supplies the address of channels
+// 4 (l & 3) .. + 3 of pixel l >> 2.
+typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+__device__ __forceinline__ bf16x8 read_pixels(const lds_bf16 *row, int o0, int o1)
 {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int n = lane & 15, g = lane >> 4;
-    int jj = 0;
-    for (int job = wave; job < 36; job += kWaves, ++jj) {
-        const int tap = job >> 2, cot = (job >> 1) & 1, cit = job & 1;
-        const int dy = tap_dy(tap), dx = tap_dx(tap);
-        f32x4 c = acc[jj];
-        for (int k0 = 0; k0 < kPix; k0 += 32) {
-            bf16x8 av, bv;
+    const s16x4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(row + o0));
+    const s16x4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(row + o1));
+    typedef short s16x8 __attribute__((ext_vector_type(8)));
+    return __builtin_bit_cast(bf16x8, (s16x8)__builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
+// dW[tap][ci][co] += sum_p X[p + tap][ci] dZ[p][co] of one 32 -> 32 layer, K =
+// the 32 pixels of a row. A wave owns one 16 x 16 block (co tile, ci tile) for
+// taps 0..4 (HALF 0) or 5..8 (HALF 1); the HALF 1 waves of the first ci tile
+// also sum dZ over the pixels (the bias gradient) against a column of ones, so
+// each SIMD carries nine or ten products per row. Each row of X is read once
+// per dx and kept for the next row's taps: eight transposing reads feed five
+// MFMAs, where gathering the operands element by element took 16 reads for
+// one (three layers of a patch: 150 us then, about 12 us now).
+template <int HALF>
+__device__ __forceinline__ void dw_rows(const lds_bf16 *X, const lds_bf16 *dZ, const int (&xo)[3][2],
+                                        const int (&zo)[2], bool bias, f32x4 (&acc)[5])
+{
+    bf16x8 ones;
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const int p = k0 + g * 8 + i;  // pixel (K index)
-                av[i] = dZ[p * kC + cot * 16 + n];                       // A[m = co][k = p]
-                const int q = wrap32((p >> 5) + dy) * kSide + wrap32((p & 31) + dx);
-                bv[i] = X[q * kC + cit * 16 + n];                        // B[k = p][n = ci]
+    for (int i = 0; i < 8; ++i) ones[i] = (__bf16)1.0f;
+    bf16x8 prev[3], cur[3];
+    // HALF 0 works on rows y - 1 (taps 0..2) and y (3, 4), HALF 1 on y (5) and
+    // y + 1 (6..8): prev is the upper of the two
+    const lds_bf16 *xrow = X + (HALF ? 0 : -1) * kActRow;
+#pragma unroll
+    for (int d = 0; d < 3; ++d) prev[d] = read_pixels(xrow, xo[d][0], xo[d][1]);
+#pragma unroll 2
+    for (int y = 0; y < kSide; ++y) {
+        xrow += kActRow;
+#pragma unroll
+        for (int d = 0; d < 3; ++d) cur[d] = read_pixels(xrow, xo[d][0], xo[d][1]);
+        const bf16x8 z = read_pixels(dZ + y * kActRow, zo[0], zo[1]);
+        if (HALF == 0) {
+            acc[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(z, prev[0], acc[0], 0, 0, 0);
+            acc[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(z, prev[1], acc[1], 0, 0, 0);
+            acc[2] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(z, prev[2], acc[2], 0, 0, 0);
+            acc[3] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(z, cur[0], acc[3], 0, 0, 0);
+            acc[4] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(z, cur[1], acc[4], 0, 0, 0);
+        } else {
+            acc[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(z, prev[2], acc[0], 0, 0, 0);
+            acc[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(z, cur[0], acc[1], 0, 0, 0);
+            acc[2] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(z, cur[1], acc[2], 0, 0, 0);
+            acc[3] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(z, cur[2], acc[3], 0, 0, 0);
+            if (bias) acc[4] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(z, ones, acc[4], 0, 0, 0);
+        }
+#pragma unroll
+        for (int d = 0; d < 3; ++d) prev[d] = cur[d];
+    }
+}
+
+// dX[p][ci] = sum_tap,co dZ[p - tap][co] W[tap][ci][co], times the ReLU mask
+// of X, written over X (halo rows included). The forward layer's scheme with
+// the taps mirrored: weights in registers as the A operand, 16 pixels of a row
+// as B, each wave eight consecutive rows of one column half, taken from the
+// last to the first so that every row adds its taps in the order t = 0..8.
+__device__ __forceinline__ void dx_rows(lds_bf16 *X, const lds_bf16 *dZ, int tid, const bf16x8 (&w)[9][2])
+{
+    typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+    typedef __attribute__((address_space(3))) bf16x8 lds_bf16x8;
+    typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n = lane & 15, g = lane >> 4;
+    const int col0 = (wave & 1) * 16 + n;
+    const int r0 = (wave >> 1) * 8;
+    const lds_bf16 *base[3];  // columns x - dx
+#pragma unroll
+    for (int d = 0; d < 3; ++d) base[d] = dZ + r0 * kActRow + act_off(wrap32(col0 - d + 1), g);
+    const int op[2] = {act_off(col0, g >> 1) + (g & 1) * 4, act_off(col0, 2 + (g >> 1)) + (g & 1) * 4};
+    lds_bf16 *obase = X + r0 * kActRow;
+    constexpr int kRows = 8;
+    f32x4 acc[3][2];
+    bf16x8 x[2][3];
+#pragma unroll
+    for (int d = 0; d < 3; ++d) x[0][d] = *reinterpret_cast<const lds_bf16x8 *>(base[d] + kRows * kActRow);
+#pragma unroll
+    for (int i = 0; i < kRows + 2; ++i) {  // row r0 + q of dZ
+        const int q = kRows - i, cur = i & 1;
+        __builtin_amdgcn_sched_barrier(0);
+        if (i + 1 < kRows + 2) {
+#pragma unroll
+            for (int d = 0; d < 3; ++d)
+                x[cur ^ 1][d] = *reinterpret_cast<const lds_bf16x8 *>(base[d] + (q - 1) * kActRow);
+        }
+#pragma unroll
+        for (int dy = -1; dy <= 1; ++dy) {
+            const int k = q + dy;  // output row whose tap dy reads row q
+            if (k < 0 || k >= kRows) continue;
+            f32x4 (&ac)[2] = acc[k % 3];
+            if (dy == -1) ac[0] = ac[1] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int d = 0; d < 3; ++d) {
+                const int t = 3 * (dy + 1) + d;
+                ac[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[t][0], x[cur][d], ac[0], 0, 0, 0);
+                ac[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[t][1], x[cur][d], ac[1], 0, 0, 0);
             }
-            c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bv, c, 0, 0, 0);
-        }
-        acc[jj] = c;
-    }
-}
-
-// dX = conv-transpose(dZ, W), times the ReLU mask of X, written over X.
-__device__ __forceinline__ void dx_mfma(__bf16 *__restrict__ X, const __bf16 *__restrict__ dZ,
-                                        const __bf16 *__restrict__ wbl)
-{
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int n = lane & 15, g = lane >> 4;
-    bf16x8 w[9][2];
+            if (dy == 1) {
 #pragma unroll
-    for (int t = 0; t < 9; ++t)
+                for (int ct = 0; ct < 2; ++ct) {
+                    lds_bf16 *o = obase + k * kActRow + op[ct];
+                    const bf16x4 a = *reinterpret_cast<const lds_bf16x4 *>(o);
+                    bf16x4 v;
 #pragma unroll
-        for (int ct = 0; ct < 2; ++ct)  // n indexes ci within tile ct; 8 consecutive co per lane
-            w[t][ct] = *reinterpret_cast<const bf16x8 *>(wbl + (t * kC + ct * 16 + n) * kC + g * 8);
-    for (int tile = wave; tile < kPix / 16; tile += kWaves) {
-        const int y = tile >> 1, x0 = (tile & 1) * 16;
-        f32x4 acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int t = 0; t < 9; ++t) {
-            // out[p] uses in[p + tap]: the gradient at p comes from dZ[p - tap]
-            const int p = wrap32(y - tap_dy(t)) * kSide + wrap32(x0 + n - tap_dx(t));
-            const bf16x8 av = *reinterpret_cast<const bf16x8 *>(dZ + p * kC + g * 8);
-            acc0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, w[t][0], acc0, 0, 0, 0);
-            acc1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, w[t][1], acc1, 0, 0, 0);
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int p = y * kSide + x0 + g * 4 + i;
-            const float m0 = (float)X[p * kC + n] > 0.0f ? 1.0f : 0.0f;
-            const float m1 = (float)X[p * kC + 16 + n] > 0.0f ? 1.0f : 0.0f;
-            X[p * kC + n] = (__bf16)(acc0[i] * m0);
-            X[p * kC + 16 + n] = (__bf16)(acc1[i] * m1);
+                    for (int j = 0; j < 4; ++j) v[j] = (__bf16)(ac[ct][j] * ((float)a[j] > 0.0f ? 1.0f : 0.0f));
+                    *reinterpret_cast<lds_bf16x4 *>(o) = v;
+                    if (k == 0 && r0 == 0) *reinterpret_cast<lds_bf16x4 *>(o + kSide * kActRow) = v;
+                    if (k == kRows - 1 && r0 == kSide - kRows)
+                        *reinterpret_cast<lds_bf16x4 *>(o - kSide * kActRow) = v;
+                }
+            }
         }
     }
 }
 
-__device__ __forceinline__ void load_act(__bf16 *__restrict__ dst, const __bf16 *__restrict__ src)
+// A stored activation plane (64 KB, [pixel][channel]) through registers into
+// an LDS buffer: thread t holds the 16-byte chunks t, t + 512, ...
+constexpr int kActVecs = kPix * kC / 8 / kT;
+__device__ __forceinline__ void fetch_act(bf16x8 (&v)[kActVecs], int tid, const __bf16 *__restrict__ src)
 {
-    const bf16x8 *s = reinterpret_cast<const bf16x8 *>(src);
-    bf16x8 *d = reinterpret_cast<bf16x8 *>(dst);
-    for (int i = threadIdx.x; i < kPix * kC / 8; i += kT) d[i] = s[i];
+    typedef __attribute__((address_space(1))) const bf16x8 glb_bf16x8;
+    glb_bf16x8 *s = (glb_bf16x8 *)src;
+#pragma unroll
+    for (int i = 0; i < kActVecs; ++i) v[i] = s[tid + i * kT];
+}
+__device__ __forceinline__ void put_chunk(lds_bf16 *dst, int chunk, bf16x8 v)
+{
+    typedef __attribute__((address_space(3))) bf16x8 lds_bf16x8;
+    const int p = chunk >> 2, o = act_off(p, chunk & 3);
+    *reinterpret_cast<lds_bf16x8 *>(dst + o) = v;
+    if (p < kSide) *reinterpret_cast<lds_bf16x8 *>(dst + o + kSide * kActRow) = v;          // row 32 = row 0
+    if (p >= kPix - kSide) *reinterpret_cast<lds_bf16x8 *>(dst + o - kSide * kActRow) = v;  // row -1 = row 31
+}
+__device__ __forceinline__ void put_act(lds_bf16 *dst, int tid, const bf16x8 (&v)[kActVecs])
+{
+#pragma unroll
+    for (int i = 0; i < kActVecs; ++i) put_chunk(dst, tid + i * kT, v[i]);
 }
 
+constexpr int kGPart = (kNParams + 1 + 3) / 4 * 4;  // gradients, then the loss; rows 16-byte aligned
+static_assert(oW2 % 4 == 0 && (9 * kC * kC + kC) % 4 == 0, "the gradient blocks are stored 16 bytes at a time");
+constexpr int kLine1 = 10 * kC;             // conv1 gradients of a row: W1[9][32], b1[32]
+
+// LDS: two activation buffers with halo rows, the centred input (halo rows),
+// the head's parameters and vectors.
+struct BwdLds {
+    static constexpr size_t kXs = 2 * (size_t)kActElems * 2;                      // byte offsets
+    static constexpr size_t kHeadPrm = kXs + (kPix + 2 * kSide) * 4;
+    static constexpr size_t kVec = kHeadPrm + ((kNHead + 3) / 4 * 4) * 4;
+    static constexpr size_t kTotal = kVec + (40 + kH + kC + 8) * 4;
+};
+static_assert(BwdLds::kTotal <= 160 * 1024, "backward LDS exceeds a CU's 160 KB");
+static_assert(kLine1 * kSide * 4 <= kActElems * 2, "the conv1 partial sums reuse an activation buffer");
+
+// Bound: at the training batch of 256 there is one patch per CU, so its time
+// is one patch's chain of phases: 6900 MFMAs (11.5 us at the full rate), the
+// 200 KB of stored activations and the barriers between the layers. The next
+// plane's activations and the dX weights are read into registers while the
+// dW products of the layer before run. Measured at batch 256: 63 us, against
+// 227 us with operands gathered element by element and the bias and conv1
+// sums on 32 and 288 threads, pixel by pixel; the whole training step with
+// the head's backward, the reduction and Adam 95 us against 380.
 __global__ __launch_bounds__(kT) void k_backward(BwdArgs a)
 {
     extern __shared__ __align__(16) unsigned char smem[];
-    __bf16 *buf0 = reinterpret_cast<__bf16 *>(smem);
-    __bf16 *buf1 = buf0 + kPix * kC;
-    float *xs = reinterpret_cast<float *>(buf1 + kPix * kC);  // [1024]
-    float *red = xs + kPix;                                   // [8]
-    float *dz1 = red + kWaves;                                // [32] scratch for bias grads
-    const int tid = threadIdx.x;
-    f32x4 acc[3][5];
+    lds_bf16 *buf0 = (lds_bf16 *)(smem) + kActRow;  // row 0 of a buffer with halo rows
+    lds_bf16 *buf1 = buf0 + kActElems;
+    float *xs = reinterpret_cast<float *>(smem + BwdLds::kXs) + kSide;
+    float *hp = reinterpret_cast<float *>(smem + BwdLds::kHeadPrm);  // parameters from oM1 on
+    float *z = reinterpret_cast<float *>(smem + BwdLds::kVec);       // [37] head input
+    float *dh = z + 40;                                              // [32] dL/d(hidden pre-activation)
+    float *dpool = dh + kH;                                          // [32]
+    float *dyv = dpool + kC;                                         // [2] dL/dy
+    int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n = tid & 15, g = (tid & 63) >> 4;
+    // dW block of this wave and the lane's operand offsets within a row
+    const int cot = wave & 1, cit = (wave >> 1) & 1, half = wave >> 2;
+    const bool bias = half == 1 && cit == 0;
+    typedef __attribute__((address_space(1))) f32x4 glb_f32x4;
+    float *gp = a.gpart + (size_t)blockIdx.x * kGPart;  // this workgroup's sums
+    int xo[3][2], zo[2];
 #pragma unroll
-    for (int l = 0; l < 3; ++l)
+    for (int h = 0; h < 2; ++h) {
+        const int px = g * 8 + h * 4 + (n >> 2), c = (n & 3) >> 1, e = (n & 1) * 4;
+        zo[h] = act_off(px, cot * 2 + c) + e;
 #pragma unroll
-        for (int j = 0; j < 5; ++j) acc[l][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    // conv1 weight/bias and conv2..4 bias gradients: thread tid owns entries
-    float gw1[1] = {0.0f};  // W1[tap][co] entry tid (tid < 288)
-    float gb[4] = {0.f, 0.f, 0.f, 0.f};  // bias of layer l for channel tid (tid < 32)
-
+        for (int d = 0; d < 3; ++d) xo[d][h] = act_off(wrap32(px + d - 1), cit * 2 + c) + e;
+    }
+    float g1 = 0.0f;                        // entry tid of (W1, b1)
+    float ghd[3] = {0.0f, 0.0f, 0.0f};      // entries tid, tid + 512, tid + 1024 of the head's gradient
+    float loss = 0.0f;                      // thread 0
+    for (int i = tid; i < kNHead; i += kT) hp[i] = a.prm[oM1 + i];
+    const size_t plane = (size_t)a.batch * kPix * kC;
     for (int b = blockIdx.x; b < a.batch; b += gridDim.x) {
-        const size_t stride = (size_t)a.batch * kPix * kC;
+        asm volatile("" : "+v"(tid));  // what follows from it is not kept over the whole loop
+        const int lane = tid & 63;
         const __bf16 *act = a.acts + (size_t)b * kPix * kC;
-        // dZ4 = dpool / 1024 where a4 > 0 (a4 from the forward)
-        load_act(buf0, act + 3 * stride);
-        __syncthreads();
-        for (int i = tid; i < kPix * kC; i += kT) {
-            const float d = a.dpool[(size_t)b * kC + (i & 31)] * (1.0f / kPix);
-            buf0[i] = (__bf16)((float)buf0[i] > 0.0f ? d : 0.0f);
-        }
-        __bf16 *dZ = buf0, *X = buf1;
-        for (int l = 3; l >= 1; --l) {  // layer l + 1 of the network: conv2..4 are l = 1..3
-            load_act(X, act + (size_t)(l - 1) * stride);
-            __syncthreads();
-            // bias gradient of this layer: sum over pixels of dZ
-            if (tid < kC) {
-                float s = 0.0f;
-                for (int p = 0; p < kPix; ++p) s += (float)dZ[p * kC + tid];
-                gb[l] += s;
-            }
-            dw_mfma(X, dZ, acc[l - 1]);
-            __syncthreads();
-            dx_mfma(X, dZ, a.wb + (size_t)(l - 1) * 9 * kC * kC);
-            __syncthreads();
-            __bf16 *t = dZ;
-            dZ = X;
-            X = t;
-        }
-        // layer 1 (1 -> 32), FP32: x from the input
-        const float *lk = a.logk + (size_t)b * kPix;
+        bf16x8 nx[kActVecs];
+        fetch_act(nx, tid, act + 2 * plane);  // a3, the input of conv4
+        unsigned mk[kActVecs];
+#pragma unroll
+        for (int i = 0; i < kActVecs; ++i) mk[i] = a.mask4[(size_t)b * kPix + ((tid + i * kT) >> 2)];
         const int sym = a.sym ? (int)a.sym[b] : 0;
+        const float *lk = a.logk + (size_t)b * kPix;
         const float v0 = lk[sym_src(tid, sym)], v1 = lk[sym_src(tid + kT, sym)];
-        const float m = block_sum_fixed(v0 + v1, red) * (1.0f / kPix);
+        if (tid < kZ) z[tid] = a.pool[(size_t)b * kZ + tid];
+        __syncthreads();
+        // ---- head, FP32: loss = mean over the batch and both outputs of
+        // (prediction - target)^2
+        const float m = z[kC];
+        if (wave == 0) {
+            const int j = lane;
+            float hpre = 0.0f, h = 0.0f;
+            if (j < kH) {
+                hpre = hp[(oC1 - oM1) + j];
+#pragma unroll
+                for (int k = 0; k < kZ; ++k) hpre += hp[j * kZ + k] * z[k];
+                h = fmaxf(hpre, 0.0f);
+            }
+            float y0 = j < kH ? hp[(oM2 - oM1) + j] * h : 0.0f, y1 = j < kH ? hp[(oM2 - oM1) + kH + j] * h : 0.0f;
+#pragma unroll
+            for (int off = 32; off >= 1; off >>= 1) {
+                y0 += __shfl_xor(y0, off, 64);
+                y1 += __shfl_xor(y1, off, 64);
+            }
+            // a transposed patch is trained on the exchanged targets
+            const int tr = sym & 1;
+            const float e0 = y0 + hp[oC2 - oM1] + m - a.target[2 * (size_t)b + tr];
+            const float e1 = y1 + hp[oC2 - oM1 + 1] + m - a.target[2 * (size_t)b + 1 - tr];
+            const float scale = 2.0f / (2.0f * a.batch);
+            const float d0 = scale * e0, d1 = scale * e1;
+            if (j == 0) {
+                dyv[0] = d0;
+                dyv[1] = d1;
+                loss += (e0 * e0 + e1 * e1) / (2.0f * a.batch);
+            }
+            if (j < kH) {
+                dh[j] = (hpre > 0.0f) ? (d0 * hp[(oM2 - oM1) + j] + d1 * hp[(oM2 - oM1) + kH + j]) : 0.0f;
+                dpool[j] = h;  // the hidden values, until their gradient is taken below
+            }
+        }
+        put_act(buf1, tid, nx);
+        fetch_act(nx, tid, act + plane);  // a2
         xs[tid] = v0 - m;
         xs[tid + kT] = v1 - m;
+        if (tid < kSide) xs[kPix + tid] = v0 - m;              // row 32 = row 0
+        if (tid >= kT - kSide) xs[tid + kT - kPix] = v1 - m;  // row -1 = row 31
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < 3; ++r) {
+            const int i = tid + r * kT;  // head parameter oM1 + i
+            if (i < oC1 - oM1)
+                ghd[r] += dh[i / kZ] * z[i % kZ];
+            else if (i < oM2 - oM1)
+                ghd[r] += dh[i - (oC1 - oM1)];
+            else if (i < oC2 - oM1)
+                ghd[r] += dyv[i >= oM2 - oM1 + kH] * dpool[(i - (oM2 - oM1)) & (kH - 1)];
+            else if (i < kNHead)
+                ghd[r] += dyv[i - (oC2 - oM1)];
+        }
         __syncthreads();
         if (tid < kC) {
             float s = 0.0f;
-            for (int p = 0; p < kPix; ++p) s += (float)dZ[p * kC + tid];
-            gb[0] += s;
-        }
-        if (tid < 9 * kC) {
-            const int tap = tid / kC, co = tid % kC;
-            const int dy = tap_dy(tap), dx = tap_dx(tap);
-            float s = 0.0f;
-            for (int p = 0; p < kPix; ++p) {
-                const int q = wrap32((p >> 5) + dy) * kSide + wrap32((p & 31) + dx);
-                s += xs[q] * (float)dZ[p * kC + co];
-            }
-            gw1[0] += s;
+#pragma unroll
+            for (int k = 0; k < kH; ++k) s += dh[k] * hp[k * kZ + tid];
+            dpool[tid] = s;
         }
         __syncthreads();
-    }
-    (void)dz1;
-    // write this workgroup's partial conv gradients
-    float *gp = a.gpart + (size_t)blockIdx.x * kNConv;
-    if (tid < 9 * kC) gp[oW1 + tid] = gw1[0];
-    if (tid < kC) {
-        gp[oB1 + tid] = gb[0];
-        gp[oB2 + tid] = gb[1];
-        gp[oB3 + tid] = gb[2];
-        gp[oB4 + tid] = gb[3];
-    }
-    const int lane = tid & 63, wave = tid >> 6;
-    const int n = lane & 15, g = lane >> 4;
+        // ---- dZ4 = dpool / 1024 where a4 > 0
 #pragma unroll
-    for (int l = 0; l < 3; ++l) {
-        float *gw = gp + oW2 + l * (9 * kC * kC + kC);  // W[tap][ci][co]
-        int jj = 0;
-        for (int job = wave; job < 36; job += kWaves, ++jj) {
-            const int tap = job >> 2, cot = (job >> 1) & 1, cit = job & 1;
+        for (int i = 0; i < kActVecs; ++i) {
+            const int chunk = tid + i * kT, c = chunk & 3;
+            // channel 16 ct + 4 k + j is bit 4 ct + j of the pixel's byte k
+            const unsigned bits = (mk[i] >> (16 * (c & 1))) >> (4 * (c >> 1));
+            bf16x8 v;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int co = cot * 16 + g * 4 + i;  // D row m = co
-                const int ci = cit * 16 + n;          // D col n = ci
-                gw[(tap * kC + ci) * kC + co] = acc[l][jj][i];
+            for (int j = 0; j < 8; ++j) {
+                const bool on = (bits >> ((j & 3) + 8 * (j >> 2))) & 1;
+                v[j] = (__bf16)(on ? dpool[c * 8 + j] * (1.0f / kPix) : 0.0f);
+            }
+            put_chunk(buf0, chunk, v);
+        }
+        __syncthreads();
+        lds_bf16 *dZ = buf0, *X = buf1;
+#pragma unroll
+        for (int l = 3; l >= 1; --l) {  // layer l + 1 of the network: conv2..4 are l = 1..3
+            typedef __attribute__((address_space(1))) const bf16x8 glb_bf16x8;
+            const __bf16 *wbl = a.wb + (size_t)(l - 1) * 9 * kC * kC;
+            asm volatile("" : "+s"(wbl));  // keeps the loads here: hoisted, three layers' weights spill
+            bf16x8 w[9][2];
+#pragma unroll
+            for (int t = 0; t < 9; ++t)
+#pragma unroll
+                for (int ct = 0; ct < 2; ++ct)
+                    w[t][ct] = *(glb_bf16x8 *)(wbl + (t * kC + ct * 16 + (lane & 15)) * kC + (lane >> 4) * 8);
+            // this wave's gradients (half 0: taps 0..4; half 1: taps 5..8 and
+            // the bias) go on from the workgroup's earlier patches
+            float *gl = gp + oW2 + (l - 1) * (9 * kC * kC + kC) + half * 5 * (kC * kC);
+            unsigned go = (cit * 16 + n) * kC + cot * 16 + g * 4, gob = cot * 16 + g * 4;
+            asm volatile("" : "+v"(go), "+v"(gob));
+            f32x4 acc[5];
+#pragma unroll
+            for (int j = 0; j < 5; ++j) {
+                acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+                if (b != (int)blockIdx.x && (j < 4 || half == 0)) acc[j] = *(glb_f32x4 *)(gl + j * (kC * kC) + go);
+                if (b != (int)blockIdx.x && j == 4 && bias) acc[j] = *(glb_f32x4 *)(gl + j * (kC * kC) + gob);
+            }
+            if (half == 0)
+                dw_rows<0>(X, dZ, xo, zo, false, acc);
+            else
+                dw_rows<1>(X, dZ, xo, zo, bias, acc);
+#pragma unroll
+            for (int j = 0; j < 5; ++j) {
+                if (j < 4 || half == 0) *(glb_f32x4 *)(gl + j * (kC * kC) + go) = acc[j];
+                if (j == 4 && bias && n == 0) *(glb_f32x4 *)(gl + j * (kC * kC) + gob) = acc[j];
+            }
+            __syncthreads();
+            dx_rows(X, dZ, tid, w);
+            __syncthreads();
+            lds_bf16 *t = dZ;
+            dZ = X;
+            X = t;
+            if (l > 1) {
+                put_act(X, tid, nx);
+                if (l == 3) fetch_act(nx, tid, act);  // a1
+                __syncthreads();
             }
         }
+        // ---- layer 1 (1 -> 32), FP32: each thread two channels of one row,
+        // with the 3 x 3 window of the input in registers
+        {
+            const int cp = tid & 15, y = tid >> 4;
+            float s[9][2], sb[2] = {0.0f, 0.0f};
+#pragma unroll
+            for (int t = 0; t < 9; ++t) s[t][0] = s[t][1] = 0.0f;
+            const float *xr = xs + y * kSide;
+            float win[3][3];  // [dy][column]
+#pragma unroll
+            for (int r = 0; r < 3; ++r) {
+                win[r][1] = xr[(r - 1) * kSide + kSide - 1];
+                win[r][2] = xr[(r - 1) * kSide];
+            }
+            const lds_bf16 *zr = dZ + y * kActRow + (cp & 3) * 2;
+#pragma unroll 8
+            for (int x = 0; x < kSide; ++x) {
+#pragma unroll
+                for (int r = 0; r < 3; ++r) {
+                    win[r][0] = win[r][1];
+                    win[r][1] = win[r][2];
+                    win[r][2] = xr[(r - 1) * kSide + wrap32(x + 1)];
+                }
+                typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+                typedef __attribute__((address_space(3))) const bf16x2 lds_bf16x2;
+                const bf16x2 dz = *(lds_bf16x2 *)(zr + act_off(x, cp >> 2));
+                const float d0 = (float)dz[0], d1 = (float)dz[1];
+                sb[0] += d0;
+                sb[1] += d1;
+#pragma unroll
+                for (int r = 0; r < 3; ++r)
+#pragma unroll
+                    for (int d = 0; d < 3; ++d) {
+                        s[3 * r + d][0] += win[r][d] * d0;
+                        s[3 * r + d][1] += win[r][d] * d1;
+                    }
+            }
+            // the row sums into the free buffer, then each entry over the rows
+            float *line = reinterpret_cast<float *>(smem) + (X == buf0 ? 0 : kActElems / 2);
+            float *o = line + y * kLine1 + 2 * cp;
+#pragma unroll
+            for (int t = 0; t < 9; ++t) {
+                o[t * kC] = s[t][0];
+                o[t * kC + 1] = s[t][1];
+            }
+            o[9 * kC] = sb[0];
+            o[9 * kC + 1] = sb[1];
+            __syncthreads();
+            if (tid < kLine1) {
+                float t = 0.0f;
+#pragma unroll 8
+                for (int r = 0; r < kSide; ++r) t += line[r * kLine1 + tid];
+                g1 += t;
+            }
+            __syncthreads();
+        }
     }
+    if (tid < kLine1) gp[oW1 + tid] = g1;  // W1, then b1
+#pragma unroll
+    for (int r = 0; r < 3; ++r)
+        if (tid + r * kT < kNHead) gp[oM1 + tid + r * kT] = ghd[r];
+    if (tid == 0) gp[kNParams] = loss;
 }
+static_assert(oB1 == oW1 + 9 * kC && oB2 == oW2 + 9 * kC * kC && oB3 == oW3 + 9 * kC * kC && oB4 == oW4 + 9 * kC * kC,
+              "each layer's bias follows its weights");
 
-// grad = sum over workgroups of the conv partials (fixed order), and the sum
-// over patches of the head gradients; loss = sum of the loss terms.
-__global__ void k_reduce(const float *__restrict__ gpart, int nparts, const float *__restrict__ ghead, int batch,
-                         const float *__restrict__ loss_terms, float *__restrict__ grad, float *__restrict__ loss)
+// Sum over the workgroups' partial gradients in workgroup order, 32 of them
+// read ahead (a loop that waited for each read took 121 us at 256 partials;
+// the sums and their order are the same). ADAM: the parameter update in the
+// same pass; else the gradient is written. The last entry is the loss.
+struct AdamArgs {
+    float *prm, *mom, *vel;
+    float lr, b1, b2, eps, c1, c2;
+};
+template <bool ADAM>
+__global__ __launch_bounds__(64) void k_reduce(const float *__restrict__ gpart, int nparts, float *__restrict__ grad,
+                                               float *__restrict__ loss, AdamArgs ad)
 {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < kNConv) {
-        float s = 0.0f;
-        for (int w = 0; w < nparts; ++w) s += gpart[(size_t)w * kNConv + i];
-        grad[i] = s;
-    } else if (i < kNParams) {
-        const int j = i - kNConv;
-        float s = 0.0f;
-        for (int b = 0; b < batch; ++b) s += ghead[(size_t)b * kNHead + j];
-        grad[i] = s;
-    } else if (i == kNParams) {
-        float s = 0.0f;
-        for (int b = 0; b < batch; ++b) s += loss_terms[b];
-        *loss = s;
+    const int i = blockIdx.x * 64 + threadIdx.x;
+    if (i > kNParams) return;
+    float mom = 0.0f, vel = 0.0f, prm = 0.0f;
+    if (ADAM && i < kNParams) {
+        mom = ad.mom[i];
+        vel = ad.vel[i];
+        prm = ad.prm[i];
     }
-}
-
-__global__ void k_adam(float *__restrict__ prm, float *__restrict__ mom, float *__restrict__ vel,
-                       const float *__restrict__ grad, float lr, float b1, float b2, float eps, float c1, float c2)
-{
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= kNParams) return;
-    const float g = grad[i];
-    const float m = b1 * mom[i] + (1.0f - b1) * g;
-    const float v = b2 * vel[i] + (1.0f - b2) * g * g;
-    mom[i] = m;
-    vel[i] = v;
-    prm[i] -= lr * (m / c1) / (sqrtf(v / c2) + eps);
+    float s = 0.0f;
+    constexpr int kAhead = 32;
+    for (int w0 = 0; w0 < nparts; w0 += kAhead) {
+        float v[kAhead];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) v[u] = gpart[(size_t)min(w0 + u, nparts - 1) * kGPart + i];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u)
+            if (w0 + u < nparts) s += v[u];
+    }
+    if (i == kNParams) {
+        if (loss) *loss = s;
+        return;
+    }
+    if (ADAM) {
+        const float m = ad.b1 * mom + (1.0f - ad.b1) * s;
+        const float v = ad.b2 * vel + (1.0f - ad.b2) * s * s;
+        ad.mom[i] = m;
+        ad.vel[i] = v;
+        ad.prm[i] = prm - ad.lr * (m / ad.c1) / (sqrtf(v / ad.c2) + ad.eps);
+    } else if (grad) {
+        grad[i] = s;
+    }
 }
 
 struct SurLayout {
-    size_t off_wf, off_wb, off_next, off_acts, off_pool, off_dpool, off_ghead, off_loss_terms, off_gpart,
-        off_grad, off_loss, off_pred, total;
+    size_t off_wf, off_wb, off_next, off_acts, off_mask4, off_pool, off_gpart, off_pred, total;
     int grid;
 };
 
@@ -1096,15 +1298,11 @@ SurLayout sur_layout(int batch, bool train)
     L.off_wb = off; off = align_up(off + 3 * 9 * kC * kC * 2);
     L.off_next = off; off = align_up(off + sizeof(int));
     if (train) {
-        L.off_acts = off;       off = align_up(off + 4 * B * kPix * kC * 2);
-        L.off_pool = off;       off = align_up(off + B * kZ * 4);
-        L.off_dpool = off;      off = align_up(off + B * kC * 4);
-        L.off_ghead = off;      off = align_up(off + B * kNHead * 4);
-        L.off_loss_terms = off; off = align_up(off + B * 4);
-        L.off_gpart = off;      off = align_up(off + (size_t)L.grid * kNConv * 4);
-        L.off_grad = off;       off = align_up(off + kNParams * 4);
-        L.off_loss = off;       off = align_up(off + 4);
-        L.off_pred = off;       off = align_up(off + B * 2 * 4);
+        L.off_acts = off;  off = align_up(off + 3 * B * kPix * kC * 2);
+        L.off_mask4 = off; off = align_up(off + B * kPix * 4);
+        L.off_pool = off;  off = align_up(off + B * kZ * 4);
+        L.off_gpart = off; off = align_up(off + (size_t)L.grid * kGPart * 4);
+        L.off_pred = off;  off = align_up(off + B * 2 * 4);
     }
     L.total = off;
     return L;
@@ -1115,7 +1313,6 @@ constexpr size_t kFwdLds = 2 * kActElems * 2 + (kPix + 2 * kSide + kWaves * kC +
 static_assert((2 * kActElems * 2 + (kPix + 2 * kSide + kWaves * kC + kWaves + kZ + 3 + 16 + 3 * kWaves) * 4) % 16 == 0,
               "the staged weights need 16-byte alignment");
 static_assert(kFwdLds + 64 <= 160 * 1024, "forward LDS exceeds a CU's 160 KB");
-constexpr size_t kBwdLds = 2 * kPix * kC * 2 + (kPix + kWaves + kC) * 4;
 
 lbm_status check_ws(void *d_ws, size_t ws_bytes, size_t need, const char *fn)
 {
@@ -1150,6 +1347,7 @@ lbm_status forward(const float *prm, int batch, const float *logk, const int8_t 
     a.pred = pred;
     a.stats = stats;
     a.acts = train ? reinterpret_cast<__bf16 *>(ws + L.off_acts) : nullptr;
+    a.mask4 = train ? reinterpret_cast<unsigned *>(ws + L.off_mask4) : nullptr;
     a.pool_out = train ? reinterpret_cast<float *>(ws + L.off_pool) : nullptr;
     a.next = reinterpret_cast<int *>(ws + L.off_next);
     LBM_HIP(hipFuncSetAttribute((const void *)k_forward<false>, hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -1166,35 +1364,36 @@ lbm_status forward(const float *prm, int batch, const float *logk, const int8_t 
     return LBM_OK;
 }
 
+// Gradients of a batch, summed over it into d_grad and d_loss (either may be
+// NULL), or, with ad, straight into an Adam step.
 lbm_status gradients(const float *prm, int batch, const float *logk, const int8_t *sym, const float *target,
-                     float *pred, char *ws, const SurLayout &L, hipStream_t stream)
+                     float *pred, float *d_grad, float *d_loss, const AdamArgs *ad, char *ws, const SurLayout &L,
+                     hipStream_t stream)
 {
     lbm_status s = pack(prm, ws, L, stream);
     if (s != LBM_OK) return s;
     s = forward(prm, batch, logk, sym, 1, pred, nullptr, ws, L, true, stream);
     if (s != LBM_OK) return s;
-    float *pool = reinterpret_cast<float *>(ws + L.off_pool);
-    float *dpool = reinterpret_cast<float *>(ws + L.off_dpool);
-    float *ghead = reinterpret_cast<float *>(ws + L.off_ghead);
-    float *lterms = reinterpret_cast<float *>(ws + L.off_loss_terms);
-    hipLaunchKernelGGL(k_head_backward, dim3(batch), dim3(64), 0, stream, prm, pool, target, sym, batch, ghead,
-                       dpool, lterms);
-    LBM_HIP(hipGetLastError());
     BwdArgs b{};
     b.prm = prm;
     b.wb = reinterpret_cast<const __bf16 *>(ws + L.off_wb);
     b.logk = logk;
     b.sym = sym;
     b.acts = reinterpret_cast<const __bf16 *>(ws + L.off_acts);
-    b.dpool = dpool;
+    b.mask4 = reinterpret_cast<const unsigned *>(ws + L.off_mask4);
+    b.pool = reinterpret_cast<const float *>(ws + L.off_pool);
+    b.target = target;
     b.batch = batch;
     b.gpart = reinterpret_cast<float *>(ws + L.off_gpart);
-    LBM_HIP(hipFuncSetAttribute((const void *)k_backward, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kBwdLds));
-    hipLaunchKernelGGL(k_backward, dim3(L.grid), dim3(kT), kBwdLds, stream, b);
+    LBM_HIP(hipFuncSetAttribute((const void *)k_backward, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                (int)BwdLds::kTotal));
+    hipLaunchKernelGGL(k_backward, dim3(L.grid), dim3(kT), BwdLds::kTotal, stream, b);
     LBM_HIP(hipGetLastError());
-    hipLaunchKernelGGL(k_reduce, dim3((kNParams + 1 + 255) / 256), dim3(256), 0, stream,
-                       reinterpret_cast<const float *>(ws + L.off_gpart), L.grid, ghead, batch, lterms,
-                       reinterpret_cast<float *>(ws + L.off_grad), reinterpret_cast<float *>(ws + L.off_loss));
+    const dim3 rg((kNParams + 1 + 63) / 64), rb(64);
+    if (ad)
+        hipLaunchKernelGGL((k_reduce<true>), rg, rb, 0, stream, b.gpart, L.grid, (float *)nullptr, d_loss, *ad);
+    else
+        hipLaunchKernelGGL((k_reduce<false>), rg, rb, 0, stream, b.gpart, L.grid, d_grad, d_loss, AdamArgs{});
     LBM_HIP(hipGetLastError());
     return LBM_OK;
 }
@@ -1323,12 +1522,7 @@ extern "C" lbm_status lbm_cnn_gradients(const float *d_params, int32_t batch, co
     lbm_status s = check_ws(d_ws, ws_bytes, L.total, "lbm_cnn_gradients");
     if (s != LBM_OK) return s;
     char *ws = static_cast<char *>(d_ws);
-    s = gradients(d_params, batch, d_logk, d_sym, d_target, d_pred, ws, L, stream);
-    if (s != LBM_OK) return s;
-    if (d_grad)
-        LBM_HIP(hipMemcpyAsync(d_grad, ws + L.off_grad, kNParams * 4, hipMemcpyDeviceToDevice, stream));
-    if (d_loss) LBM_HIP(hipMemcpyAsync(d_loss, ws + L.off_loss, 4, hipMemcpyDeviceToDevice, stream));
-    return LBM_OK;
+    return gradients(d_params, batch, d_logk, d_sym, d_target, d_pred, d_grad, d_loss, nullptr, ws, L, stream);
 }
 
 extern "C" lbm_status lbm_cnn_train_step(float *d_params, float *d_adam_m, float *d_adam_v, int32_t step, float lr,
@@ -1343,13 +1537,8 @@ extern "C" lbm_status lbm_cnn_train_step(float *d_params, float *d_adam_m, float
     if (s != LBM_OK) return s;
     char *ws = static_cast<char *>(d_ws);
     float *pred = reinterpret_cast<float *>(ws + L.off_pred);
-    s = gradients(d_params, batch, d_logk, d_sym, d_target, pred, ws, L, stream);
-    if (s != LBM_OK) return s;
     const float b1 = 0.9f, b2 = 0.999f;
     const float c1 = 1.0f - std::pow(b1, (float)step), c2 = 1.0f - std::pow(b2, (float)step);
-    hipLaunchKernelGGL(k_adam, dim3((kNParams + 255) / 256), dim3(256), 0, stream, d_params, d_adam_m, d_adam_v,
-                       reinterpret_cast<const float *>(ws + L.off_grad), lr, b1, b2, 1e-8f, c1, c2);
-    LBM_HIP(hipGetLastError());
-    if (d_loss) LBM_HIP(hipMemcpyAsync(d_loss, ws + L.off_loss, 4, hipMemcpyDeviceToDevice, stream));
-    return LBM_OK;
+    const AdamArgs ad{d_params, d_adam_m, d_adam_v, lr, b1, b2, 1e-8f, c1, c2};
+    return gradients(d_params, batch, d_logk, d_sym, d_target, pred, nullptr, d_loss, &ad, ws, L, stream);
 }
