@@ -4,8 +4,8 @@
 // populations from its neighbours (streaming of Eq. f-evolution-of-S-C read
 // backwards), collides them in registers and writes the nine new
 // post-collision values to its own cell. k_step does one step per pass over
-// HBM; k_stepd does D = 2, 4 or 6 steps per pass, the intermediate steps
-// staying in LDS (temporal blocking, bit-identical to D single steps).
+// HBM; k_tile and k_rows do several steps per pass, the intermediate steps
+// staying on chip (temporal blocking, bit-identical to single steps).
 // The state in memory is therefore the post-collision populations of the
 // previous step; the pre-collision populations at the current step are the
 // pulled ones, which is what lbm_fields and lbm_get_populations report.
@@ -32,8 +32,6 @@
 // literal transcription. The collision arithmetic is FP64 for both storage
 // types; FP32 storage only rounds the nine values written per cell.
 #include <hip/hip_runtime.h>
-
-#include <array>
 
 #include <cmath>
 #include <cstring>
@@ -248,25 +246,36 @@ __device__ __forceinline__ void collide_guo(const StepArgs<R> &a, double f[9], i
         hgx = a.hegx_d;
         hgy = a.hegy_d;
     }
-    const double cnu = (double)cm.ld(0, c);
-    const double den = rho * (1.0 + 0.5 * cnu);
-    const double ux = (jx + hgx * rho) / den, uy = (jy + hgy * rho) / den;
-    // rho f_m = rho (eps G - (eps nu / kappa) u)
-    const double fmx = rho * (2.0 * hgx - cnu * ux), fmy = rho * (2.0 * hgy - cnu * uy);
-    const double om = a.om_d;
-    const double kf = 3.0 * (1.0 - 0.5 * om);  // (1 - 1/(2 tau)) / c_s^2
-    const double ru3x = 3.0 * rho * ux, ru3y = 3.0 * rho * uy;
-    // deviations: f~eq_a = w_a (dr + 3 rho e_a . u), F_a = w_a kf e_a . rho f_m
-    const double w0 = 4.0 / 9.0, w1 = 1.0 / 9.0, w5 = 1.0 / 36.0;
-    f[0] = f[0] + om * (w0 * dr - f[0]);
-    f[1] = f[1] + om * (w1 * (dr + ru3x) - f[1]) + w1 * kf * fmx;
-    f[2] = f[2] + om * (w1 * (dr + ru3y) - f[2]) + w1 * kf * fmy;
-    f[3] = f[3] + om * (w1 * (dr - ru3x) - f[3]) - w1 * kf * fmx;
-    f[4] = f[4] + om * (w1 * (dr - ru3y) - f[4]) - w1 * kf * fmy;
-    f[5] = f[5] + om * (w5 * (dr + ru3x + ru3y) - f[5]) + w5 * kf * (fmx + fmy);
-    f[6] = f[6] + om * (w5 * (dr - ru3x + ru3y) - f[6]) + w5 * kf * (fmy - fmx);
-    f[7] = f[7] + om * (w5 * (dr - ru3x - ru3y) - f[7]) - w5 * kf * (fmx + fmy);
-    f[8] = f[8] + om * (w5 * (dr + ru3x - ru3y) - f[8]) + w5 * kf * (fmx - fmy);
+    {
+        // every fused multiply-add written out and no other contraction, so
+        // that all kernels round alike
+#pragma clang fp contract(off)
+        const double cnu = (double)cm.ld(0, c);
+        const double den = rho * __builtin_fma(0.5, cnu, 1.0);
+        const double ux = __builtin_fma(hgx, rho, jx) / den, uy = __builtin_fma(hgy, rho, jy) / den;
+        // rho f_m = rho (eps G - (eps nu / kappa) u)
+        const double tx = __builtin_fma(-cnu, ux, 2.0 * hgx), ty = __builtin_fma(-cnu, uy, 2.0 * hgy);
+        const double fmx = rho * tx, fmy = rho * ty;
+        const double om = a.om_d;
+        const double kf = 3.0 * __builtin_fma(-0.5, om, 1.0);  // (1 - 1/(2 tau)) / c_s^2
+        const double r3 = 3.0 * rho;
+        // deviations: f~eq_a = w_a (dr + 3 rho e_a . u), F_a = w_a kf e_a . rho f_m
+        const double w0 = 4.0 / 9.0, w1 = 1.0 / 9.0, w5 = 1.0 / 36.0;
+        const double k1 = w1 * kf, k5 = w5 * kf;
+        const double px = __builtin_fma(r3, ux, dr), mx = __builtin_fma(-r3, ux, dr);
+        const double py = __builtin_fma(r3, uy, dr), my = __builtin_fma(-r3, uy, dr);
+        auto relax = [&](double fa, double w, double e) { return __builtin_fma(om, __builtin_fma(w, e, -fa), fa); };
+        f[0] = relax(f[0], w0, dr);
+        f[1] = __builtin_fma(k1, fmx, relax(f[1], w1, px));
+        f[2] = __builtin_fma(k1, fmy, relax(f[2], w1, py));
+        f[3] = __builtin_fma(-k1, fmx, relax(f[3], w1, mx));
+        f[4] = __builtin_fma(-k1, fmy, relax(f[4], w1, my));
+        const double s5 = __builtin_fma(rho, tx, fmy);
+        f[5] = __builtin_fma(k5, s5, relax(f[5], w5, __builtin_fma(r3, uy, px)));
+        f[6] = __builtin_fma(k5, __builtin_fma(-rho, tx, fmy), relax(f[6], w5, __builtin_fma(r3, uy, mx)));
+        f[7] = __builtin_fma(-k5, s5, relax(f[7], w5, __builtin_fma(-r3, uy, mx)));
+        f[8] = __builtin_fma(k5, __builtin_fma(rho, tx, -fmy), relax(f[8], w5, __builtin_fma(-r3, uy, px)));
+    }
 }
 
 // Coefficient sources besides the plane accessors: one value already in a
@@ -435,233 +444,366 @@ __global__ __launch_bounds__(kBlock) void k_step(StepArgs<R> a)
     for (int q = 0; q < 9; ++q) o[q * S + c] = (R)f[q];
 }
 
-// Tiles of the multi-step kernel, per storage type and depth D (time steps
-// per launch): TX x TY output cells per workgroup of BS threads. The LDS
-// holds one buffer of 9 x (TX + 2 (D - 1)) x (TY + 2 (D - 1)) values.
-#ifndef LBM_DEEP
-#define LBM_DEEP 6  // steps per launch of the deepest kernel (FP32 state)
-#endif
-#ifndef LBM_TILE6
-#define LBM_TILE6 48, 24, 512
-#endif
-#ifndef LBM_TILE4
-#define LBM_TILE4 64, 16, 512
-#endif
-template <int X, int Y, int B> struct TileShape { static constexpr int TX = X, TY = Y, BS = B; };
-template <typename R, int D> struct TileD;
-template <> struct TileD<float, 2> : TileShape<64, 64, 1024> {};
-template <> struct TileD<float, 4> : TileShape<LBM_TILE4> {};
-template <> struct TileD<float, LBM_DEEP> : TileShape<LBM_TILE6> {};
-constexpr int kDeep = LBM_DEEP;
-static_assert(kDeep > 4, "the deepest kernel must take more than 4 steps");
-#ifndef LBM_TILE6D
-#define LBM_TILE6D 32, 12, 256
-#endif
-#ifndef LBM_TILE4D
-#define LBM_TILE4D 32, 16, 256
-#endif
-template <> struct TileD<double, 2> : TileShape<32, 16, 256> {};
-template <> struct TileD<double, 4> : TileShape<LBM_TILE4D> {};
-template <> struct TileD<double, LBM_DEEP> : TileShape<LBM_TILE6D> {};
-// Per arithmetic type A: FP32 collision arithmetic needs 61 VGPRs where FP64
-// needs 96, so two 768-thread workgroups (24 waves) fit a CU beside each
-// other's 80 KB of LDS. Measured per six-step launch on 2048^2 (us): 50 x 24
-// on 768 threads 89.8, 48 x 24 90.8, 56 x 20 90.7; 48 x 24 on 512 99.3, on
-// 704 103.0, on 640, 832, 896 or 1024 threads 138-153; five steps per launch
-// with 56 x 24 on 768 97.6.
-#ifndef LBM_TILE6F
-#define LBM_TILE6F 50, 24, 768
-#endif
-#ifndef LBM_TILE4F
-#define LBM_TILE4F 64, 20, 768  // four-step launches (us, 2048^2): 81.0 against 88.6 for 64 x 16 on 512
-#endif
-template <typename R, int D, typename A> struct TileDA : TileD<R, D> {};
-template <> struct TileDA<float, LBM_DEEP, float> : TileShape<LBM_TILE6F> {};
-template <> struct TileDA<float, 4, float> : TileShape<LBM_TILE4F> {};
-#ifndef LBM_TILE2F
-#define LBM_TILE2F 96, 18, 768  // two-step launches (us, 2048^2): 66.0 against 74.3 for 64 x 64 on 1024
-#endif
-template <> struct TileDA<float, 2, float> : TileShape<LBM_TILE2F> {};
-// Seven steps per launch, FP32 collision arithmetic only (the depth the
-// launch planner takes for most steps of that path): per launch on 2048^2
-// (us) 36 x 28 on 768 threads 98.8 (14.1 per step against 14.9 at six
-// steps), 48 x 22 99.9, 40 x 26 101.3, 42 x 24 102.7, 44 x 22 104.7,
-// 32 x 32 105.4; eight steps with 30 x 30 120.4.
-constexpr int kDeeper = 7;
-#ifndef LBM_TILE7F
-#define LBM_TILE7F 36, 28, 768
-#endif
-template <> struct TileDA<float, kDeeper, float> : TileShape<LBM_TILE7F> {};
+// Several time steps per launch (temporal blocking). A workgroup owns a tile of
+// output cells and takes step t on the tile plus a (D - 1)-cell halo, pulling
+// from HBM; steps t + 1 .. t + D - 2 run on regions that shrink by one cell per
+// step, on chip; step t + D - 1 runs on the tile and writes to HBM. Every
+// value is rounded to the storage type exactly where a store to HBM would
+// round it, so the result is bit-identical to D one-step launches, while HBM
+// sees one read and one write of the state per D steps (plus the halo, which
+// neighbouring tiles mostly find in L2).
+//
+// Each thread owns the same cells in every step: their rest populations and
+// coefficients (drag, and the force per cell) stay in its registers, read once
+// per launch. The eight moving populations live in LDS, one plane each,
+// streamed in place: after a step that leaves each cell's own post-collision
+// values in its own slots, the next step reads f_a from (a, x - e_a) and
+// writes f*_opp(a) to that same slot, and the step after reads its own slots
+// reversed and writes them in order again. A step's reads and writes touch the
+// same slots and no cell shares one, so a step needs one barrier and one copy
+// of the state. (The kernel before this one copied the state through
+// registers between two barriers, recomputed its cells' coordinates in every
+// step and, with a force or a tensor, read the coefficients from L2 in every
+// step.)
+template <typename R>
+struct RegCoef {
+    R v[4];
+    __device__ R ld(int q, int) const { return v[q]; }
+};
+constexpr int kLdsPad = 72;  // elements before and after the LDS planes: the row above a tile's first cell
+__device__ constexpr int kOpp[9] = {0, 3, 4, 1, 2, 7, 8, 5, 6};
 
-// D time steps per launch (temporal blocking). Phase 1 takes step t on the
-// workgroup's tile plus a (D - 1)-cell halo, pulling from HBM and keeping the
-// post-collision values in LDS, rounded to the storage type exactly as a
-// store to HBM would round them; phases 2 .. D - 1 take the next steps on
-// regions that shrink by one cell per step, in place in LDS; phase D takes the
-// last step on the tile and writes to HBM. The result is bit-identical to D
-// one-step launches while HBM sees one read and one write of the state per D
-// steps (plus the halo, which neighbouring tiles mostly find in L2). Loads and
-// stores go through BMem (32-bit offsets, plane bases in scalar registers).
-template <typename R, bool WALLS, int PK, bool FF, int D, typename A = double, bool GY = true>
-__global__ __launch_bounds__((TileDA<R, D, A>::BS)) void k_stepd(StepArgs<R> a)
+// Any tile tx x ty whose halo tile fits BS x KM cells, any depth D >= 2. AXC: the
+// halo tile's row length at compile time, or 0. Used where the grid is small
+// (one tile per CU, see plan_launches) and for FP64 state.
+template <typename R, bool WALLS, int PK, bool FF, int BS, int KM, int AXC, typename A>
+__global__ __launch_bounds__(BS) void k_tile(StepArgs<R> a, int D, int tx, int ty)
 {
-    constexpr int TX = TileDA<R, D, A>::TX, TY = TileDA<R, D, A>::TY, BS = TileDA<R, D, A>::BS;
-    constexpr int H = D - 1;
-    constexpr int AX = TX + 2 * H, AY = TY + 2 * H, AN = AX * AY;
-    constexpr int KM = (D > 2) ? ((AX - 2) * (AY - 2) + BS - 1) / BS : 1;  // cells per thread, phase 2
-    // scalar coefficients without a force field are read once from HBM and
-    // kept in LDS next to the populations
-    constexpr bool CL = (PK != 4) && !FF && 10 * AN * sizeof(R) <= 160 * 1024;
-    // FP32 arithmetic keeps 2E there (the exact factor 2 of the collision)
-    constexpr bool E2 = CL && PK == 1 && sizeof(A) == 4 && sizeof(R) == 4;
-    static_assert(GY || E2, "the variant without a y drive is the FP32 scalar one");
-    __shared__ R P[9][AN];
-    __shared__ R Dl[CL ? AN : 1];
+    constexpr int CAP = BS * KM;
+    __shared__ R lds[8 * CAP + 2 * kLdsPad];
+    R *S = lds + kLdsPad;
     const int nx = a.nx, ny = a.ny;
-    const int ntx = (nx + TX - 1) / TX;
+    const int H = D - 1, AX = AXC ? AXC : tx + 2 * H;
+    const int ntx = (nx + tx - 1) / tx;
     const int bid = xcd_block(blockIdx.x, gridDim.x);
-    const int y0 = (bid / ntx) * TY, x0 = (bid % ntx) * TX;
-    const int tw = min(TX, nx - x0), th = min(TY, ny - y0);  // ragged tiles at the far edges
+    const int x0 = (bid % ntx) * tx, y0 = (bid / ntx) * ty;
+    const int w1 = min(tx, nx - x0) + 2 * H, h1 = min(ty, ny - y0) + 2 * H;  // ragged tiles at the far edges
     const BMem<R> mem{a.fin, a.fout, a.stride};
-    // Interior tiles (most of a large grid): every cell the launch touches,
-    // including the neighbours phase 1 pulls from, lies inside the grid away
-    // from the walls, so no wrap, wall or ragged-edge test is needed.
-    const bool interior = tw == TX && th == TY && x0 >= H + 1 && x0 + TX + H <= nx - 1 &&
-                          y0 >= H + 1 && y0 + TY + H <= ny - 1;
-    // lattice cell of P coordinate (px, py); false beyond a wall
-    // (x0 - H + px lies in [-H, nx + H): one wrap suffices unless the grid
-    // is narrower than the halo)
-    const bool wide = nx > H, tall = ny > H;
-    auto cell_of = [&](int px, int py, int &x, int &y) -> bool {
-        x = x0 - H + px;
-        if (wide) {
-            x = x < 0 ? x + nx : (x >= nx ? x - nx : x);
-        } else {
-            x %= nx;
-            x = x < 0 ? x + nx : x;
-        }
-        y = y0 - H + py;
-        if (WALLS) return y >= 0 && y < ny;
-        if (tall) {
-            y = y < 0 ? y + ny : (y >= ny ? y - ny : y);
-        } else {
-            y %= ny;
-            y = y < 0 ? y + ny : y;
-        }
-        return true;
-    };
-    // the nine pre-collision values of P cell c (lattice row y) from the buffer
-    auto pull_lds = [&](int c, int y, bool edge, A f[9]) {
-        const bool lo = WALLS && edge && y == 0, hi = WALLS && edge && y == ny - 1;
-        f[0] = (A)P[0][c];
-        f[1] = (A)P[1][c - 1];
-        f[3] = (A)P[3][c + 1];
-        f[2] = (A)(lo ? P[4][c] : P[2][c - AX]);
-        f[5] = (A)(lo ? P[7][c] : P[5][c - AX - 1]);
-        f[6] = (A)(lo ? P[8][c] : P[6][c - AX + 1]);
-        f[4] = (A)(hi ? P[2][c] : P[4][c + AX]);
-        f[7] = (A)(hi ? P[5][c] : P[7][c + AX + 1]);
-        f[8] = (A)(hi ? P[6][c] : P[8][c + AX - 1]);
-    };
-    const int w1 = tw + 2 * H, h1 = th + 2 * H;
-    auto body = [&](auto fast_tag) {
-        constexpr bool FAST = decltype(fast_tag)::value;
-        // phase 1: region [0, tw + 2H) x [0, th + 2H) from HBM
-        for (int i = threadIdx.x; i < AN; i += BS) {
+    // every cell the launch touches lies inside the grid, away from the walls
+    const bool interior = x0 >= H + 1 && x0 + w1 - H <= nx - 1 && y0 >= H + 1 && y0 + h1 - H <= ny - 1;
+    auto body = [&](auto interior_tag) {
+        constexpr bool EDGE = !decltype(interior_tag)::value;
+        constexpr bool WB = WALLS && EDGE;
+        int depth[KM];  // the last step (0-based) this cell takes part in; < 0: none
+        int cell[KM];
+        bool lo[KM], hi[KM];  // against the lower, upper wall
+        R f0[KM];
+        RegCoef<R> cf[KM], fc[KM];
+#pragma unroll
+        for (int k = 0; k < KM; ++k) {
+            const int i = threadIdx.x + k * BS;
             const int px = i % AX, py = i / AX;
-            int x, y;
-            R fr[9];
-            if constexpr (FAST) {
-                x = x0 - H + px;
-                y = y0 - H + py;
-                const int c = y * nx + x;
-                fr[0] = mem.ld(0, c);
-                fr[1] = mem.ld(1, c - 1);
-                fr[3] = mem.ld(3, c + 1);
-                fr[2] = mem.ld(2, c - nx);
-                fr[5] = mem.ld(5, c - nx - 1);
-                fr[6] = mem.ld(6, c - nx + 1);
-                fr[4] = mem.ld(4, c + nx);
-                fr[7] = mem.ld(7, c + nx + 1);
-                fr[8] = mem.ld(8, c + nx - 1);
-            } else {
-                if (px >= w1 || py >= h1 || !cell_of(px, py, x, y)) continue;
-                pullm<R, WALLS>(mem, nx, ny, x, y, fr);
-            }
-            A f[9];
-#pragma unroll
-            for (int q = 0; q < 9; ++q) f[q] = (A)fr[q];
-            if constexpr (CL) {
-                const R d0 = BMem<R>{a.coef, nullptr, a.cstride}.ld(0, y * nx + x);
-                const R d = E2 ? d0 + d0 : d0;
-                Dl[i] = d;
-                collide_m<R, PK, FF, E2, GY>(a, f, 0, 0, OneCoef<R>{d}, OneCoef<R>{d});
-            } else {
-                collide_cell<R, PK, FF, BMem<R>>(a, f, y * nx + x);
-            }
-#pragma unroll
-            for (int q = 0; q < 9; ++q) P[q][i] = (R)f[q];
-        }
-        // phases 2 .. D - 1: region [ph, w1 - ph) x [ph, h1 - ph), in place;
-        // threads walk the full-tile shape (compile-time divisors) and skip
-        // the part a ragged tile lacks
-#pragma unroll
-        for (int ph = 1; ph < H; ++ph) {
-            const int RW = AX - 2 * ph, RN = RW * (AY - 2 * ph);
-            __syncthreads();
-            R pr[KM][9];
-#pragma unroll
-            for (int k = 0; k < KM; ++k) {
-                const int i = threadIdx.x + k * BS;
-                const int px = ph + i % RW, py = ph + i / RW;
-                int x = x0 - H + px, y = y0 - H + py;
-                const bool in = FAST ? i < RN
-                                     : (i < RN && px < w1 - ph && py < h1 - ph && cell_of(px, py, x, y));
-                if (in) {
-                    A f[9];
-                    pull_lds(py * AX + px, y, !FAST, f);
-#pragma unroll
-                    for (int q = 0; q < 9; ++q) pr[k][q] = (R)f[q];
+            int x = x0 - H + px, y = y0 - H + py;
+            bool in = px < w1 && py < h1;
+            if (EDGE) {
+                x %= nx;
+                x = x < 0 ? x + nx : x;
+                if (WALLS) {
+                    in = in && y >= 0 && y < ny;
+                } else {
+                    y %= ny;
+                    y = y < 0 ? y + ny : y;
                 }
             }
+            depth[k] = in ? min(min(px, w1 - 1 - px), min(py, h1 - 1 - py)) : -1;
+            lo[k] = WB && y == 0;
+            hi[k] = WB && y == ny - 1;
+            const int c = y * nx + x;
+            cell[k] = c;
+            if (in) {
+                R fr[9];
+                if constexpr (EDGE) {
+                    pullm<R, WALLS>(mem, nx, ny, x, y, fr);
+                } else {
+                    fr[0] = mem.ld(0, c);
+                    fr[1] = mem.ld(1, c - 1);
+                    fr[3] = mem.ld(3, c + 1);
+                    fr[2] = mem.ld(2, c - nx);
+                    fr[5] = mem.ld(5, c - nx - 1);
+                    fr[6] = mem.ld(6, c - nx + 1);
+                    fr[4] = mem.ld(4, c + nx);
+                    fr[7] = mem.ld(7, c + nx + 1);
+                    fr[8] = mem.ld(8, c + nx - 1);
+                }
+                const BMem<R> cm{a.coef, nullptr, a.cstride}, fm{a.hforce, nullptr, a.cstride};
+#pragma unroll
+                for (int q = 0; q < (PK == 4 ? 4 : 1); ++q) cf[k].v[q] = cm.ld(q, c);
+                if (FF) {
+                    fc[k].v[0] = fm.ld(0, c);
+                    fc[k].v[1] = fm.ld(1, c);
+                }
+                A f[9];
+#pragma unroll
+                for (int q = 0; q < 9; ++q) f[q] = (A)fr[q];
+                collide_m<R, PK, FF>(a, f, 0, 0, cf[k], fc[k]);
+                f0[k] = (R)f[0];
+#pragma unroll
+                for (int q = 1; q < 9; ++q) S[(q - 1) * CAP + i] = (R)f[q];
+            }
+        }
+        // the slots a cell's neighbours (or, against a wall, the cell itself)
+        // hold for it after a step in own order
+        auto slots = [&](int k, int (&r)[9]) {
+            const int c = threadIdx.x + k * BS;
+            r[1] = 0 * CAP + c - 1;
+            r[3] = 2 * CAP + c + 1;
+            r[2] = lo[k] ? 3 * CAP + c : 1 * CAP + c - AX;
+            r[5] = lo[k] ? 6 * CAP + c : 4 * CAP + c - AX - 1;
+            r[6] = lo[k] ? 7 * CAP + c : 5 * CAP + c - AX + 1;
+            r[4] = hi[k] ? 1 * CAP + c : 3 * CAP + c + AX;
+            r[7] = hi[k] ? 4 * CAP + c : 6 * CAP + c + AX + 1;
+            r[8] = hi[k] ? 5 * CAP + c : 7 * CAP + c + AX - 1;
+        };
+        for (int s = 1; s < H; ++s) {
             __syncthreads();
+            if (s & 1) {
+#pragma unroll
+                for (int k = 0; k < KM; ++k)
+                    if (depth[k] >= s) {
+                        A f[9];
+                        int r[9];
+                        slots(k, r);
+                        f[0] = (A)f0[k];
+#pragma unroll
+                        for (int q = 1; q < 9; ++q) f[q] = (A)S[r[q]];
+                        collide_m<R, PK, FF>(a, f, 0, 0, cf[k], fc[k]);
+#pragma unroll
+                        for (int q = 1; q < 9; ++q) S[r[q]] = (R)f[kOpp[q]];
+                        f0[k] = (R)f[0];
+                    }
+            } else {
+#pragma unroll
+                for (int k = 0; k < KM; ++k)
+                    if (depth[k] >= s) {
+                        A f[9];
+                        const int c = threadIdx.x + k * BS;
+                        f[0] = (A)f0[k];
+#pragma unroll
+                        for (int q = 1; q < 9; ++q) f[q] = (A)S[(kOpp[q] - 1) * CAP + c];
+                        collide_m<R, PK, FF>(a, f, 0, 0, cf[k], fc[k]);
+#pragma unroll
+                        for (int q = 1; q < 9; ++q) S[(q - 1) * CAP + c] = (R)f[q];
+                        f0[k] = (R)f[0];
+                    }
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < KM; ++k)
+            if (depth[k] >= H) {
+                A f[9];
+                f[0] = (A)f0[k];
+                if (H & 1) {
+                    int r[9];
+                    slots(k, r);
+#pragma unroll
+                    for (int q = 1; q < 9; ++q) f[q] = (A)S[r[q]];
+                } else {
+#pragma unroll
+                    for (int q = 1; q < 9; ++q) f[q] = (A)S[(kOpp[q] - 1) * CAP + threadIdx.x + k * BS];
+                }
+                collide_m<R, PK, FF>(a, f, 0, 0, cf[k], fc[k]);
+#pragma unroll
+                for (int q = 0; q < 9; ++q) mem.st(q, cell[k], (R)f[q]);
+            }
+    };
+    if (AXC != 0 && interior)
+        body(std::true_type{});
+    else
+        body(std::false_type{});
+}
+
+// The same with halo tiles of 64 x (BS KM / 64) cells, a wave holding whole
+// rows: which rows take part in a step, and the walls, are then uniform over
+// the wave (scalar branches), all LDS offsets are compile-time constants, and
+// a step skips the rows it no longer needs without idle lanes. For large grids
+// with FP32 state; two workgroups of 768 threads fill a CU (73.7 KB of LDS
+// each). WPE: waves per SIMD the registers must allow.
+template <bool WALLS, int PK, bool FF, int BS, int KM, int WPE, typename A, bool GY>
+__global__ __launch_bounds__(BS, WPE) void k_rows(StepArgs<float> a, int D)
+{
+    using R = float;
+    constexpr int CAP = BS * KM, NWV = BS / 64, AX = 64, AY = CAP / 64;
+    // FP32 arithmetic keeps 2E (the exact factor 2 of the collision)
+    constexpr bool E2 = PK == 1 && !FF && sizeof(A) == 4;
+    static_assert(GY || E2, "the variant without a y drive is the FP32 scalar one");
+    __shared__ R lds[8 * CAP + 2 * kLdsPad];
+    const int H = D - 1, tx = AX - 2 * H, ty = AY - 2 * H;
+    const int nx = a.nx, ny = a.ny;
+    const int ntx = (nx + tx - 1) / tx;
+    const int bid = xcd_block(blockIdx.x, gridDim.x);
+    const int tr = bid / ntx;
+    const int x0 = (bid - tr * ntx) * tx, y0 = tr * ty;
+    const int w1 = min(tx, nx - x0) + 2 * H, h1 = min(ty, ny - y0) + 2 * H;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    R *S = lds + kLdsPad + threadIdx.x;
+    const int dcol = min(lane, w1 - 1 - lane);
+    const bool interior = x0 >= H + 1 && x0 + w1 - H <= nx - 1 && y0 >= H + 1 && y0 + h1 - H <= ny - 1;
+    auto body = [&](auto interior_tag) {
+        constexpr bool EDGE = !decltype(interior_tag)::value;
+        constexpr bool WB = WALLS && EDGE;
+        R f0[KM];
+        RegCoef<R> cf[KM], fc[KM];
+        auto row_y = [&](int k) { return y0 - H + wv + k * NWV; };
+        auto row_depth = [&](int k) {  // the last step row k of this wave takes part in; < 0: none
+            const int py = wv + k * NWV;
+            const int d = min(py, h1 - 1 - py);
+            return WB && (row_y(k) < 0 || row_y(k) >= ny) ? -1 : d;
+        };
+        if (dcol >= 0) {
+            int x = x0 - H + lane;
+            if (EDGE) {
+                x %= nx;
+                x = x < 0 ? x + nx : x;
+            }
+            const int xm = EDGE && x == 0 ? nx - 1 : x - 1, xp = EDGE && x == nx - 1 ? 0 : x + 1;
+            // one buffer resource per row: its base in scalar registers, a lane's offset its x
+            auto ld = [&](const R *p, int stride, int q, int row, int xx) -> R {
+                const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
+                    (void *)(p + (size_t)q * stride + (size_t)row * nx), 0, nx * (int)sizeof(R), BMem<R>::kFlags);
+                return __builtin_bit_cast(R, __builtin_amdgcn_raw_buffer_load_b32(r, xx * 4, 0, 0));
+            };
 #pragma unroll
             for (int k = 0; k < KM; ++k) {
-                const int i = threadIdx.x + k * BS;
-                const int px = ph + i % RW, py = ph + i / RW;
-                int x = x0 - H + px, y = y0 - H + py;
-                const bool in = FAST ? i < RN
-                                     : (i < RN && px < w1 - ph && py < h1 - ph && cell_of(px, py, x, y));
-                if (in) {
-                    A f[9];
+                if (row_depth(k) < 0) continue;
+                int y = row_y(k);
+                if (EDGE && !WALLS) {
+                    y %= ny;
+                    y = y < 0 ? y + ny : y;
+                }
+                const bool lo = WB && y == 0, hi = WB && y == ny - 1;
+                const int ym = EDGE && y == 0 ? ny - 1 : y - 1, yp = EDGE && y == ny - 1 ? 0 : y + 1;
+                R fr[9];
+                fr[0] = ld(a.fin, a.stride, 0, y, x);
+                fr[1] = ld(a.fin, a.stride, 1, y, xm);
+                fr[3] = ld(a.fin, a.stride, 3, y, xp);
+                fr[2] = lo ? ld(a.fin, a.stride, 4, y, x) : ld(a.fin, a.stride, 2, ym, x);
+                fr[5] = lo ? ld(a.fin, a.stride, 7, y, x) : ld(a.fin, a.stride, 5, ym, xm);
+                fr[6] = lo ? ld(a.fin, a.stride, 8, y, x) : ld(a.fin, a.stride, 6, ym, xp);
+                fr[4] = hi ? ld(a.fin, a.stride, 2, y, x) : ld(a.fin, a.stride, 4, yp, x);
+                fr[7] = hi ? ld(a.fin, a.stride, 5, y, x) : ld(a.fin, a.stride, 7, yp, xp);
+                fr[8] = hi ? ld(a.fin, a.stride, 6, y, x) : ld(a.fin, a.stride, 8, yp, xm);
 #pragma unroll
-                    for (int q = 0; q < 9; ++q) f[q] = (A)pr[k][q];
-                    const int c = py * AX + px;
-                    if constexpr (CL)
-                        collide_m<R, PK, FF, E2, GY>(a, f, c, c, LdsCoef<R>{Dl}, LdsCoef<R>{Dl});
-                    else
-                        collide_cell<R, PK, FF, BMem<R>>(a, f, y * nx + x);
+                for (int q = 0; q < (PK == 4 ? 4 : 1); ++q) cf[k].v[q] = ld(a.coef, a.cstride, q, y, x);
+                if (E2) cf[k].v[0] += cf[k].v[0];
+                if (FF) {
+                    fc[k].v[0] = ld(a.hforce, a.cstride, 0, y, x);
+                    fc[k].v[1] = ld(a.hforce, a.cstride, 1, y, x);
+                }
+                A f[9];
 #pragma unroll
-                    for (int q = 0; q < 9; ++q) P[q][c] = (R)f[q];
+                for (int q = 0; q < 9; ++q) f[q] = (A)fr[q];
+                collide_m<R, PK, FF, E2, GY>(a, f, 0, 0, cf[k], fc[k]);
+                f0[k] = (R)f[0];
+#pragma unroll
+                for (int q = 1; q < 9; ++q) S[(q - 1) * CAP + k * BS] = (R)f[q];
+            }
+        }
+        auto neighbour_step = [&](int k, A (&f)[9], auto store) {
+            R *P = S + k * BS;
+            const bool lo = WB && row_y(k) == 0, hi = WB && row_y(k) == ny - 1;
+            f[0] = (A)f0[k];
+            f[1] = (A)P[0 * CAP - 1];
+            f[3] = (A)P[2 * CAP + 1];
+            if (WB && lo) {
+                f[2] = (A)P[3 * CAP];
+                f[5] = (A)P[6 * CAP];
+                f[6] = (A)P[7 * CAP];
+            } else {
+                f[2] = (A)P[1 * CAP - AX];
+                f[5] = (A)P[4 * CAP - AX - 1];
+                f[6] = (A)P[5 * CAP - AX + 1];
+            }
+            if (WB && hi) {
+                f[4] = (A)P[1 * CAP];
+                f[7] = (A)P[4 * CAP];
+                f[8] = (A)P[5 * CAP];
+            } else {
+                f[4] = (A)P[3 * CAP + AX];
+                f[7] = (A)P[6 * CAP + AX + 1];
+                f[8] = (A)P[7 * CAP + AX - 1];
+            }
+            collide_m<R, PK, FF, E2, GY>(a, f, 0, 0, cf[k], fc[k]);
+            if constexpr (decltype(store)::value) {
+                P[0 * CAP - 1] = (R)f[3];
+                P[2 * CAP + 1] = (R)f[1];
+                if (WB && lo) {
+                    P[3 * CAP] = (R)f[4];
+                    P[6 * CAP] = (R)f[7];
+                    P[7 * CAP] = (R)f[8];
+                } else {
+                    P[1 * CAP - AX] = (R)f[4];
+                    P[4 * CAP - AX - 1] = (R)f[7];
+                    P[5 * CAP - AX + 1] = (R)f[8];
+                }
+                if (WB && hi) {
+                    P[1 * CAP] = (R)f[2];
+                    P[4 * CAP] = (R)f[5];
+                    P[5 * CAP] = (R)f[6];
+                } else {
+                    P[3 * CAP + AX] = (R)f[2];
+                    P[6 * CAP + AX + 1] = (R)f[5];
+                    P[7 * CAP + AX - 1] = (R)f[6];
+                }
+                f0[k] = (R)f[0];
+            }
+        };
+        auto own_step = [&](int k, A (&f)[9], auto store) {
+            R *P = S + k * BS;
+            f[0] = (A)f0[k];
+#pragma unroll
+            for (int q = 1; q < 9; ++q) f[q] = (A)P[(kOpp[q] - 1) * CAP];
+            collide_m<R, PK, FF, E2, GY>(a, f, 0, 0, cf[k], fc[k]);
+            if constexpr (decltype(store)::value) {
+#pragma unroll
+                for (int q = 1; q < 9; ++q) P[(q - 1) * CAP] = (R)f[q];
+                f0[k] = (R)f[0];
+            }
+        };
+        for (int s = 1; s < H; ++s) {
+            __syncthreads();
+            if (dcol >= s) {
+                if (s & 1) {
+#pragma unroll
+                    for (int k = 0; k < KM; ++k)
+                        if (row_depth(k) >= s) {
+                            A f[9];
+                            neighbour_step(k, f, std::true_type{});
+                        }
+                } else {
+#pragma unroll
+                    for (int k = 0; k < KM; ++k)
+                        if (row_depth(k) >= s) {
+                            A f[9];
+                            own_step(k, f, std::true_type{});
+                        }
                 }
             }
         }
         __syncthreads();
-        // phase D: the tile, from LDS to HBM
-        for (int i = threadIdx.x; i < TX * TY; i += BS) {
-            const int lx = i % TX, ly = i / TX;
-            if (!FAST && (lx >= tw || ly >= th)) continue;
-            const int x = x0 + lx, y = y0 + ly;
-            A f[9];
-            const int c = (ly + H) * AX + (lx + H);
-            pull_lds(c, y, !FAST, f);
-            const int g = y * nx + x;
-            if constexpr (CL)
-                collide_m<R, PK, FF, E2, GY>(a, f, c, c, LdsCoef<R>{Dl}, LdsCoef<R>{Dl});
-            else
-                collide_cell<R, PK, FF, BMem<R>>(a, f, g);
+        if (dcol >= H) {
 #pragma unroll
-            for (int q = 0; q < 9; ++q) mem.st(q, g, (R)f[q]);
+            for (int k = 0; k < KM; ++k)
+                if (row_depth(k) >= H) {
+                    A f[9];
+                    if (H & 1)
+                        neighbour_step(k, f, std::false_type{});
+                    else
+                        own_step(k, f, std::false_type{});
+                    const BMem<R> row{nullptr, a.fout + (size_t)row_y(k) * nx, a.stride};
+#pragma unroll
+                    for (int q = 0; q < 9; ++q) row.st(q, x0 - H + lane, (R)f[q]);
+                }
         }
     };
     if (interior)
@@ -952,9 +1094,34 @@ Layout layout_of(const lbm_params *p)
 }  // namespace
 }  // namespace lbm
 
+namespace lbm {
+namespace {
+
+// The kernels that take several steps per launch: k_tile with 512, 1024 or
+// 1024 x 2 cells, with 512 x 2 cells in rows of 32 (FP64 state), k_rows with
+// 768 x 3 or 1024 x 2 cells (FP32 state).
+enum Shape { kTile512, kTile1024, kTile2048, kTile32, kRows768, kRows1024, kShapes };
+constexpr int kMaxDepth = 12;   // steps per launch
+constexpr int kPlanRoom = 64;   // longest stretch planned launch by launch
+
+struct Launch {
+    int shape, tx, ty;
+    double us;  // predicted
+};
+
+struct Plan {
+    Launch at[kMaxDepth + 1];              // per depth
+    signed char first[kPlanRoom + 1];      // depth of the first launch over this many steps
+    int longest;                           // the depth of least time per step
+};
+
+}  // namespace
+}  // namespace lbm
+
 struct lbm_handle {
     lbm_params p;
     lbm::Layout L;
+    lbm::Plan plan;
     hipStream_t stream;
     char *ws;
     int cur;            // 0: state in buffer A, 1: in buffer B
@@ -1055,75 +1222,131 @@ struct StepFn {
 };
 template <typename R, bool W, int PK, bool FF>
 struct StepDFn {
-    template <int D>
-    static void launch(const lbm_handle *h)
+    template <typename A>
+    static void launch(const lbm_handle *h, int D)
     {
-        if constexpr (std::is_same<R, float>::value && PK != 0) {
-            if (h->p.pop_dtype == LBM_F32_FAST) {
-                using TF = TileDA<R, D, float>;
-                const int fx = (h->p.nx + TF::TX - 1) / TF::TX, fy = (h->p.ny + TF::TY - 1) / TF::TY;
-                const StepArgs<R> sa = step_args<R>(h);
+        const Launch &l = h->plan.at[D];
+        const int nt = ((h->p.nx + l.tx - 1) / l.tx) * ((h->p.ny + l.ty - 1) / l.ty);
+        const StepArgs<R> sa = step_args<R>(h);
+        auto tile = [&](auto kernel, int threads) {
+            hipLaunchKernelGGL(kernel, dim3(nt), dim3(threads), 0, h->stream, sa, D, l.tx, l.ty);
+        };
+        if (l.shape == kTile512) return tile(k_tile<R, W, PK, FF, 512, 1, 0, A>, 512);
+        if (l.shape == kTile1024) return tile(k_tile<R, W, PK, FF, 1024, 1, 0, A>, 1024);
+        if (l.shape == kTile2048) return tile(k_tile<R, W, PK, FF, 1024, 2, 0, A>, 1024);
+        if constexpr (std::is_same<R, double>::value) {
+            tile(k_tile<R, W, PK, FF, 512, 2, 32, A>, 512);
+        } else {
+            auto rows = [&](auto kernel, int threads) {
+                hipLaunchKernelGGL(kernel, dim3(nt), dim3(threads), 0, h->stream, sa, D);
+            };
+            if constexpr (sizeof(A) == 8) {
+                // six waves per SIMD (two workgroups per CU), but for a tensor, whose four
+                // coefficients per cell would spill (2048^2: 36.0 us per step against 31.2)
+                rows(k_rows<W, PK, FF, 768, 3, PK == 4 ? 1 : 6, A, true>, 768);
+            } else {
                 if constexpr (PK == 1 && !FF) {
-                    if ((float)sa.hegy == 0.0f) {  // drive along x only
-                        hipLaunchKernelGGL((k_stepd<R, W, PK, FF, D, float, false>), dim3(fx * fy), dim3(TF::BS), 0,
-                                           h->stream, sa);
-                        return;
+                    if (sa.hegy == 0.0f) {  // drive along x only
+                        if (l.shape == kRows1024) return rows(k_rows<W, PK, FF, 1024, 2, 8, A, false>, 1024);
+                        return rows(k_rows<W, PK, FF, 768, 3, 6, A, false>, 768);
                     }
                 }
-                hipLaunchKernelGGL((k_stepd<R, W, PK, FF, D, float>), dim3(fx * fy), dim3(TF::BS), 0, h->stream, sa);
-                return;
+                if (l.shape == kRows1024) return rows(k_rows<W, PK, FF, 1024, 2, 8, A, true>, 1024);
+                rows(k_rows<W, PK, FF, 768, 3, 6, A, true>, 768);
             }
         }
-        if constexpr (D != kDeeper) {  // seven steps: FP32 collision arithmetic only
-            constexpr int TX = TileD<R, D>::TX, TY = TileD<R, D>::TY, BS = TileD<R, D>::BS;
-            const int ntx = (h->p.nx + TX - 1) / TX, nty = (h->p.ny + TY - 1) / TY;
-            hipLaunchKernelGGL((k_stepd<R, W, PK, FF, D>), dim3(ntx * nty), dim3(BS), 0, h->stream,
-                               step_args<R>(h));
-        }
     }
-    static void run(const lbm_handle *h, int depth)
+    static void run(const lbm_handle *h, int D)
     {
-        if (depth == kDeeper) return launch<kDeeper>(h);
-        if (depth == kDeep) return launch<kDeep>(h);
-        if (depth == 4) return launch<4>(h);
-        launch<2>(h);
+        if constexpr (std::is_same<R, float>::value && PK != 0) {
+            if (h->p.pop_dtype == LBM_F32_FAST) return launch<float>(h, D);
+        }
+        launch<double>(h, D);
     }
 };
 
-// Steps per launch before the next check (or the end), `room` steps away; 1
-// runs the single-step kernel. Every depth gives the same state bit for bit,
-// so the choice is one of time only. With FP32 collision arithmetic, whose
-// seven-step kernel takes fewer microseconds per step than the six-step one,
-// the plan of launches that covers `room` in the least time by the launch
-// costs measured on 2048^2 (us: 1 step 54.5, 2: 66.0, 4: 76.8, 6: 89.2,
-// 7: 98.8): seven-step launches while more than 60 steps remain, then the
-// best mix for the rest (e.g. 100 = 10 x 7 + 5 x 6, 1434 us against 1505 for
-// 16 x 6 + 4; 20 = 7 + 7 + 6, 287 us against 334 for 6 + 6 + 6 + 2).
-// Otherwise the deepest depth that fits.
+// Predicted time (us) of one launch of depth D on tiles tx x ty of a shape:
+// a launch's own 2.7 us, the state through HBM once at 8 TB/s, and per round of
+// resident tiles the D steps, each `wave` us per wavefront and SIMD in it (at
+// least the 0.42 us that one step's chain of LDS reads, collision, writes and
+// barrier takes). Fitted to launches of 64^2 to 2048^2 grids; within 10% of
+// them: 64^2 FP32 state D = 10 6.9 us (measured 7.0), 400^2 FP64 with a force
+// D = 8 14.3 (14.8), 700^2 FP32 D = 8 22.1 (22.4), 1000^2 FP32 arithmetic D = 7
+// 24.6 (24.4), 2048^2 FP64 D = 6 179 (184).
+double launch_us(const lbm_params &p, bool force, int shape, int D, int tx, int ty)
+{
+    const bool f64 = p.pop_dtype == LBM_F64, fast = p.pop_dtype == LBM_F32_FAST;
+    const double nt = (double)((p.nx + tx - 1) / tx) * ((p.ny + ty - 1) / ty);
+    const double cus = std::max(1, device_cu_count());
+    const int ax = tx + 2 * (D - 1), ay = ty + 2 * (D - 1);
+    const bool two = shape == kRows768 || shape == kRows1024 || shape == kTile32;
+    const double r = (two && nt > cus) ? 2.0 : 1.0;  // tiles of a CU at once
+    // rounds of tiles; a last one that fills at most half of the places runs one tile per CU
+    const double full = nt / (cus * r), frac = full - std::floor(full);
+    const double rounds = full > 4.0 ? full + 0.2
+                                     : std::floor(full) + (frac == 0.0 ? 0.0 : (r == 2.0 && frac <= 0.5) ? 0.6 : 1.0);
+    const double wave = fast ? 0.063 : p.scheme == LBM_SCHEME_GUO ? 0.185 : f64 ? 0.127 : 0.112;
+    double t = r == 1.0 && rounds > 1.0 ? 2.0 : 0.0;  // a lone tile waits for its own reads
+    const double lat = r == 1.0 || full <= 1.0 ? 0.25 : 0.12;
+    for (int s = 0; s < D; ++s) t += std::max(0.42, lat + wave * r * ax * (ay - 2 * s) / 256.0);
+    const double planes = 19.0 + (force ? 2.0 : 0.0) + (p.perm_kind == LBM_PERM_TENSOR ? 3.0 : 0.0);
+    return 2.7 + rounds * t + (double)p.nx * p.ny * planes * (f64 ? 8.0 : 4.0) / 8.0e6;
+}
+
+// Per depth, the shape and tile of least predicted time; then the sequence of
+// depths that covers a stretch of up to kPlanRoom steps in the least time
+// (longer stretches start with the depth of least time per step). Every depth
+// and tile gives the same state bit for bit, so the plan is one of time only.
+// What it comes to: small grids take tiles just large enough that all run at
+// once, one per CU, ten or so steps per launch (64^2 FP32 state: 2.38 -> 0.70 us
+// per step against 48 x 24 tiles on 6 CUs); large ones the 64-wide rows with FP32
+// state (2048^2: FP32 arithmetic 15.0 -> 13.1, FP64 arithmetic 19.3 -> 17.6) and
+// 32-wide tiles with FP64 state (38.7 -> 30.7).
+Plan plan_launches(const lbm_params &p, bool force)
+{
+    Plan pl{};
+    const bool f64 = p.pop_dtype == LBM_F64, fast = p.pop_dtype == LBM_F32_FAST;
+    for (int D = 2; D <= kMaxDepth; ++D) {
+        Launch best{kTile1024, 1, 1, 1e30};
+        auto offer = [&](int shape, int tx, int ty) {
+            const double us = launch_us(p, force, shape, D, tx, ty);
+            if (us < best.us) best = Launch{shape, tx, ty, us};
+        };
+        const int h2 = 2 * (D - 1);
+        const int cap[3] = {512, 1024, 2048}, shape[3] = {kTile512, kTile1024, kTile2048};
+        for (int i = 0; i < 3; ++i)
+            for (int w = 4; w <= 64 && w + h2 <= cap[i]; ++w) {
+                const int tx = (p.nx + (p.nx + w - 1) / w - 1) / ((p.nx + w - 1) / w);  // even columns of tiles
+                const int room = cap[i] / (tx + h2) - h2;
+                if (room < 1) break;
+                const int nty = (p.ny + room - 1) / room;
+                offer(shape[i], tx, (p.ny + nty - 1) / nty);
+            }
+        if (f64 && D <= 10) offer(kTile32, 32 - h2, 32 - h2);
+        if (!f64 && D <= 10) offer(kRows768, 64 - h2, 36 - h2);
+        if (fast && D <= 10) offer(kRows1024, 64 - h2, 32 - h2);
+        pl.at[D] = best;
+    }
+    const double el = f64 ? 8.0 : 4.0;
+    pl.at[1].us = 2.7 + (double)p.nx * p.ny * 19.0 * el / 5.0e6;
+    double best[kPlanRoom + 1] = {};
+    for (int r = 1; r <= kPlanRoom; ++r) {
+        best[r] = 1e30;
+        for (int D = 1; D <= std::min(r, kMaxDepth); ++D)
+            if (pl.at[D].us + best[r - D] < best[r]) {
+                best[r] = pl.at[D].us + best[r - D];
+                pl.first[r] = (signed char)D;
+            }
+    }
+    pl.longest = 1;
+    for (int D = 2; D <= kMaxDepth; ++D)
+        if (pl.at[D].us / D < pl.at[pl.longest].us / pl.longest) pl.longest = D;
+    return pl;
+}
+
 int launch_depth(const lbm_handle *h, int64_t room)
 {
-    if (h->p.pop_dtype == LBM_F32_FAST) {
-        static const std::array<signed char, 61> first = [] {
-            const int depth[5] = {kDeeper, kDeep, 4, 2, 1};
-            const double cost[5] = {98.8, 89.2, 76.8, 66.0, 54.5};
-            std::array<double, 61> best{};
-            std::array<signed char, 61> f{};
-            for (int r = 1; r <= 60; ++r) {
-                best[r] = 1e30;
-                for (int i = 0; i < 5; ++i)
-                    if (depth[i] <= r && cost[i] + best[r - depth[i]] < best[r]) {
-                        best[r] = cost[i] + best[r - depth[i]];
-                        f[r] = (signed char)depth[i];
-                    }
-            }
-            return f;
-        }();
-        if (room > 60) return kDeeper;
-        return room >= 1 ? first[room] : 1;
-    }
-    if (room >= kDeep) return kDeep;
-    if (room >= 4) return 4;
-    return room >= 2 ? 2 : 1;
+    return room > kPlanRoom ? h->plan.longest : h->plan.first[std::max<int64_t>(room, 1)];
 }
 template <typename R, bool W, int PK, bool FF>
 struct FieldsFn {
@@ -1184,6 +1407,7 @@ extern "C" lbm_status lbm_init(lbm_handle **out, const lbm_params *p, const doub
     h->ws = static_cast<char *>(d_ws);
     h->cur = 0;
     h->has_force = d_force != nullptr;
+    h->plan = plan_launches(*p, h->has_force);
     if (hipHostMalloc((void **)&h->host_res, 4 * sizeof(double), hipHostMallocDefault) != hipSuccess) {
         delete h;
         return set_error(LBM_EDEVICE, "lbm_init: hipHostMalloc failed");
