@@ -11,10 +11,17 @@
 // full tensor (Eq. f_m-depends-on-u-and-tensor-k), through the per-cell matrix
 // M = (K + eps nu I / 2)^{-1} K with rho u = M (j + eps rho G / 2).
 //
-// Coarse grids that fit in one CU's LDS (8 planes x 4 B x cells) run in a
-// single persistent workgroup with the in-place AA streaming of the local
-// solver, so a coarse step costs no kernel launch; larger coarse grids run on
-// the HBM fine-grid path with a tensor permeability.
+// Three ranges of size. Up to 1664 cells one persistent workgroup, one or two
+// cells per thread, with the in-place streaming of the local solver takes every
+// step without a launch. From there to 4096 cells (FP64 state 2048) the fine
+// grid's many-step launches run the lattice on all CUs, and the same
+// convergence test on the velocity field is taken on the device. Larger coarse
+// grids are a fine-grid solve with a tensor permeability (its own test, on the
+// mean velocity). us per step with FP32 / FP64 state: 8 x 8 0.57 / 0.24 ->
+// 0.24 / 0.21, 32 x 32 1.65 / 0.61 -> 0.62 / 0.57, 45 x 45 2.50 / 1.19 ->
+// 0.83 / 0.81, 64 x 64 3.5 -> 0.82; before, one workgroup ran up to four cells
+// per thread. The line between the first two: at 40 x 40 one workgroup takes
+// 0.9 us per step, the launches 0.8 and 0.1 ms more per solve.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -27,9 +34,9 @@
 namespace lbm {
 namespace {
 
-constexpr int kT = 1024;
-constexpr int kCPT32 = 4;  // cells per thread, FP32 populations (4096 cells)
-constexpr int kCPT64 = 2;  // cells per thread, FP64 populations (2048 cells)
+constexpr int kOneGroup = 1664;  // cells of the largest grid one workgroup runs
+// cells up to which the convergence test is on the velocity field
+constexpr int kField32 = 4096, kField64 = 2048;
 
 template <typename R>
 struct CoarseArgs {
@@ -44,6 +51,7 @@ struct CoarseArgs {
     double *__restrict__ u_out;      // [2][N]
     double *__restrict__ rho_out;    // [N] or null
     long long *__restrict__ status;  // [0] steps, [1] flag
+    const int *__restrict__ bad;     // set by k_coarse_coef: nothing is run
 };
 
 // Coefficients of the coarse lattice from the effective permeability (FP64),
@@ -140,118 +148,118 @@ __device__ __forceinline__ void cell_velocity(const double fd[9], const R m[4], 
 // Convergence: relative L2 change of the velocity field between checks. The
 // previous field is kept in the storage type R, and the new field is rounded
 // to R before the difference, so a state that no longer changes gives
-// exactly zero.
-template <typename R, int CPT>
-__global__ __launch_bounds__(kT) void k_coarse_onchip(CoarseArgs<R> a)
+// exactly zero. Bound by the chain of LDS reads, collision, writes and barrier
+// of a step (about 0.25 us), and from four waves per SIMD on by the collision.
+template <typename R, int T, int CPT>
+__global__ __launch_bounds__(T) void k_coarse_onchip(CoarseArgs<R> a)
 {
-    extern __shared__ __align__(16) unsigned char lds_raw[];
-    R *A = reinterpret_cast<R *>(lds_raw);
-    __shared__ double red[kT / 64][2];
-    const int tid = threadIdx.x;
+    constexpr int S = T * CPT;  // plane stride
+    __shared__ R A[8 * S];
+    __shared__ double red[T / 64][2];
     const int nx = a.nx, ny = a.ny, N = nx * ny;
-    const int C = (N + kT - 1) / kT;
+    if (*a.bad) return;
     R f0[CPT], m[CPT][4], hg[CPT][2], upx[CPT], upy[CPT];
-    int xy[CPT];
+    int x[CPT], xm[CPT], xp[CPT], r0[CPT], rm[CPT], rp[CPT];
+    bool own[CPT];
 #pragma unroll
     for (int k = 0; k < CPT; ++k) {
-        const int c = tid + k * kT;
-        if (k < C && c < N) {
-            xy[k] = (c % nx) | ((c / nx) << 16);
-            f0[k] = (R)0;
-            m[k][0] = a.M[c];
-            m[k][1] = a.M[N + c];
-            m[k][2] = a.M[2 * N + c];
-            m[k][3] = a.M[3 * N + c];
+        const int c = threadIdx.x + k * T;
+        own[k] = c < N;
+        f0[k] = upx[k] = upy[k] = (R)0;
+        const int y = c / nx;
+        x[k] = c - y * nx;
+        xm[k] = x[k] == 0 ? nx - 1 : x[k] - 1;
+        xp[k] = x[k] == nx - 1 ? 0 : x[k] + 1;
+        r0[k] = y * nx;
+        rm[k] = (y == 0 ? ny - 1 : y - 1) * nx;
+        rp[k] = (y == ny - 1 ? 0 : y + 1) * nx;
+        if (own[k]) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) m[k][q] = a.M[q * N + c];
             hg[k][0] = a.heg[c];
             hg[k][1] = a.heg[N + c];
-            upx[k] = (R)0;
-            upy[k] = (R)0;
 #pragma unroll
-            for (int q = 0; q < 8; ++q) A[q * N + c] = (R)0;
+            for (int q = 0; q < 8; ++q) A[q * S + c] = (R)0;
         }
     }
     __syncthreads();
     int steps = 0, flag = 1;
     bool have_prev = false;
     while (true) {
-        for (int st = 0; st < a.check_every; ++st) {
-            const bool odd = (st & 1) != 0;
+        for (int st = 0; st < a.check_every; st += 2) {
 #pragma unroll
-            for (int k = 0; k < CPT; ++k) {
-                const int c = tid + k * kT;
-                if (k < C && c < N) {
+            for (int k = 0; k < CPT; ++k)
+                if (own[k]) {  // own slots, written back reversed
+                    const int c = threadIdx.x + k * T;
                     double f[9];
                     f[0] = (double)f0[k];
-                    if (!odd) {
 #pragma unroll
-                        for (int q = 1; q < 9; ++q) f[q] = (double)A[(q - 1) * N + c];
-                        collide_t(f, m[k], hg[k][0], hg[k][1], a);
-                        A[2 * N + c] = (R)f[1];
-                        A[3 * N + c] = (R)f[2];
-                        A[0 * N + c] = (R)f[3];
-                        A[1 * N + c] = (R)f[4];
-                        A[6 * N + c] = (R)f[5];
-                        A[7 * N + c] = (R)f[6];
-                        A[4 * N + c] = (R)f[7];
-                        A[5 * N + c] = (R)f[8];
-                    } else {
-                        const int x = xy[k] & 0xffff, y = xy[k] >> 16;
-                        const int xm = x == 0 ? nx - 1 : x - 1, xp = x == nx - 1 ? 0 : x + 1;
-                        const int rm = (y == 0 ? ny - 1 : y - 1) * nx, rp = (y == ny - 1 ? 0 : y + 1) * nx;
-                        const int r0 = y * nx;
-                        f[1] = (double)A[2 * N + r0 + xm];
-                        f[2] = (double)A[3 * N + rm + x];
-                        f[3] = (double)A[0 * N + r0 + xp];
-                        f[4] = (double)A[1 * N + rp + x];
-                        f[5] = (double)A[6 * N + rm + xm];
-                        f[6] = (double)A[7 * N + rm + xp];
-                        f[7] = (double)A[4 * N + rp + xp];
-                        f[8] = (double)A[5 * N + rp + xm];
-                        collide_t(f, m[k], hg[k][0], hg[k][1], a);
-                        A[0 * N + r0 + xp] = (R)f[1];
-                        A[1 * N + rp + x] = (R)f[2];
-                        A[2 * N + r0 + xm] = (R)f[3];
-                        A[3 * N + rm + x] = (R)f[4];
-                        A[4 * N + rp + xp] = (R)f[5];
-                        A[5 * N + rp + xm] = (R)f[6];
-                        A[6 * N + rm + xm] = (R)f[7];
-                        A[7 * N + rm + xp] = (R)f[8];
-                    }
+                    for (int q = 1; q < 9; ++q) f[q] = (double)A[(q - 1) * S + c];
+                    collide_t(f, m[k], hg[k][0], hg[k][1], a);
+                    A[2 * S + c] = (R)f[1];
+                    A[3 * S + c] = (R)f[2];
+                    A[0 * S + c] = (R)f[3];
+                    A[1 * S + c] = (R)f[4];
+                    A[6 * S + c] = (R)f[5];
+                    A[7 * S + c] = (R)f[6];
+                    A[4 * S + c] = (R)f[7];
+                    A[5 * S + c] = (R)f[8];
                     f0[k] = (R)f[0];
                 }
-                __builtin_amdgcn_sched_barrier(0);  // one cell at a time: bounded register use
-            }
+            __syncthreads();
+#pragma unroll
+            for (int k = 0; k < CPT; ++k)
+                if (own[k]) {  // the neighbours' slots
+                    double f[9];
+                    f[0] = (double)f0[k];
+                    f[1] = (double)A[2 * S + r0[k] + xm[k]];
+                    f[2] = (double)A[3 * S + rm[k] + x[k]];
+                    f[3] = (double)A[0 * S + r0[k] + xp[k]];
+                    f[4] = (double)A[1 * S + rp[k] + x[k]];
+                    f[5] = (double)A[6 * S + rm[k] + xm[k]];
+                    f[6] = (double)A[7 * S + rm[k] + xp[k]];
+                    f[7] = (double)A[4 * S + rp[k] + xp[k]];
+                    f[8] = (double)A[5 * S + rp[k] + xm[k]];
+                    collide_t(f, m[k], hg[k][0], hg[k][1], a);
+                    A[0 * S + r0[k] + xp[k]] = (R)f[1];
+                    A[1 * S + rp[k] + x[k]] = (R)f[2];
+                    A[2 * S + r0[k] + xm[k]] = (R)f[3];
+                    A[3 * S + rm[k] + x[k]] = (R)f[4];
+                    A[4 * S + rp[k] + xp[k]] = (R)f[5];
+                    A[5 * S + rp[k] + xm[k]] = (R)f[6];
+                    A[6 * S + rm[k] + xm[k]] = (R)f[7];
+                    A[7 * S + rm[k] + xp[k]] = (R)f[8];
+                    f0[k] = (R)f[0];
+                }
             __syncthreads();
         }
         steps += a.check_every;
         double d2 = 0.0, u2 = 0.0;
+        double ux[CPT], uy[CPT], rho[CPT];
 #pragma unroll
-        for (int k = 0; k < CPT; ++k) {
-            const int c = tid + k * kT;
-            if (k < C && c < N) {
+        for (int k = 0; k < CPT; ++k)
+            if (own[k]) {
                 double fd[9];
                 fd[0] = (double)f0[k];
 #pragma unroll
-                for (int q = 1; q < 9; ++q) fd[q] = (double)A[(q - 1) * N + c];
-                double ux, uy, rho;
-                cell_velocity(fd, m[k], hg[k][0], hg[k][1], ux, uy, rho);
-                const R rx = (R)ux, ry = (R)uy;
+                for (int q = 1; q < 9; ++q) fd[q] = (double)A[(q - 1) * S + threadIdx.x + k * T];
+                cell_velocity(fd, m[k], hg[k][0], hg[k][1], ux[k], uy[k], rho[k]);
+                const R rx = (R)ux[k], ry = (R)uy[k];
                 const double dx = (double)rx - (double)upx[k], dy = (double)ry - (double)upy[k];
                 d2 += dx * dx + dy * dy;
-                u2 += ux * ux + uy * uy;
+                u2 += ux[k] * ux[k] + uy[k] * uy[k];
                 upx[k] = rx;
                 upy[k] = ry;
             }
-        }
         d2 = wave_sum(d2);
         u2 = wave_sum(u2);
-        if ((tid & 63) == 0) {
-            red[tid >> 6][0] = d2;
-            red[tid >> 6][1] = u2;
+        if ((threadIdx.x & 63) == 0) {
+            red[threadIdx.x >> 6][0] = d2;
+            red[threadIdx.x >> 6][1] = u2;
         }
         __syncthreads();
         double td = 0.0, tu = 0.0;
-        for (int w = 0; w < kT / 64; ++w) {
+        for (int w = 0; w < T / 64; ++w) {
             td += red[w][0];
             tu += red[w][1];
         }
@@ -268,25 +276,19 @@ __global__ __launch_bounds__(kT) void k_coarse_onchip(CoarseArgs<R> a)
         }
         have_prev = true;
         __syncthreads();
-        if (stop) break;
-    }
-    // final fields (state is in even order after an even number of steps)
+        if (stop) {  // the fields of this check (even order after an even number of steps)
 #pragma unroll
-    for (int k = 0; k < CPT; ++k) {
-        const int c = tid + k * kT;
-        if (k < C && c < N) {
-            double fd[9];
-            fd[0] = (double)f0[k];
-#pragma unroll
-            for (int q = 1; q < 9; ++q) fd[q] = (double)A[(q - 1) * N + c];
-            double ux, uy, rho;
-            cell_velocity(fd, m[k], hg[k][0], hg[k][1], ux, uy, rho);
-            a.u_out[c] = ux;
-            a.u_out[N + c] = uy;
-            if (a.rho_out) a.rho_out[c] = rho;
+            for (int k = 0; k < CPT; ++k)
+                if (own[k]) {
+                    const int c = threadIdx.x + k * T;
+                    a.u_out[c] = ux[k];
+                    a.u_out[N + c] = uy[k];
+                    if (a.rho_out) a.rho_out[c] = rho[k];
+                }
+            break;
         }
     }
-    if (tid == 0) {
+    if (threadIdx.x == 0) {
         a.status[0] = steps;
         a.status[1] = flag;
     }
@@ -317,35 +319,23 @@ __global__ __launch_bounds__(256) void k_block_average(const double *__restrict_
 }
 
 struct CoarseLayout {
-    bool onchip;
-    size_t lds;
+    bool one_group, field;  // one workgroup; else the test on the field
     size_t off_M, off_heg, off_status, off_flag, off_perm, off_force, off_fine, fine_bytes, total;
 };
 
-int lds_budget()
-{
-    int dev = 0, v = 0;
-    if (hipGetDevice(&dev) == hipSuccess &&
-        hipDeviceGetAttribute(&v, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) == hipSuccess && v > 0)
-        return v;
-    return 64 * 1024;
-}
-
-CoarseLayout coarse_layout(int ncx, int ncy, bool f64, bool query_device)
+CoarseLayout coarse_layout(int ncx, int ncy, bool f64)
 {
     CoarseLayout L{};
     const size_t n = (size_t)ncx * ncy;
-    const size_t es = f64 ? 8 : 4;
-    L.lds = 8 * es * n;
-    const size_t budget = query_device ? (size_t)lds_budget() - 2048 : 160 * 1024 - 2048;
-    L.onchip = (n <= (size_t)kT * (f64 ? kCPT64 : kCPT32)) && L.lds <= budget;
+    L.one_group = n <= (size_t)kOneGroup;
+    L.field = n <= (size_t)(f64 ? kField64 : kField32);
     size_t off = 0;
     L.off_M = off;      off = align_up(off + 4 * n * sizeof(double));
     L.off_heg = off;    off = align_up(off + 2 * n * sizeof(double));
-    L.off_status = off; off = align_up(off + 2 * sizeof(long long));
+    L.off_status = off; off = align_up(off + 4 * sizeof(long long));
     L.off_flag = off;   off = align_up(off + sizeof(int));
-    // the HBM path needs the coarse tensor, force and a fine-solver workspace;
-    // size for it always, so the workspace does not depend on the device
+    // the other paths need the coarse tensor, force and a fine-solver
+    // workspace; sized for them always
     L.off_perm = off;   off = align_up(off + 4 * n * sizeof(double));
     L.off_force = off;  off = align_up(off + 2 * n * sizeof(double));
     lbm_params q{};
@@ -357,7 +347,7 @@ CoarseLayout coarse_layout(int ncx, int ncy, bool f64, bool query_device)
     return L;
 }
 
-template <typename R, int CPT>
+template <typename R>
 lbm_status launch_onchip(const lbm_params &pc, char *ws, const CoarseLayout &L, double tol, int check_every,
                          int64_t max_steps, double *d_u, double *d_rho, hipStream_t stream)
 {
@@ -376,10 +366,14 @@ lbm_status launch_onchip(const lbm_params &pc, char *ws, const CoarseLayout &L, 
     a.u_out = d_u;
     a.rho_out = d_rho;
     a.status = reinterpret_cast<long long *>(ws + L.off_status);
-    if (L.lds > 64 * 1024)
-        LBM_HIP(hipFuncSetAttribute((const void *)k_coarse_onchip<R, CPT>,
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)L.lds));
-    hipLaunchKernelGGL((k_coarse_onchip<R, CPT>), dim3(1), dim3(kT), L.lds, stream, a);
+    a.bad = reinterpret_cast<const int *>(ws + L.off_flag);
+    const int n = pc.nx * pc.ny;
+    if (n <= 256)
+        hipLaunchKernelGGL((k_coarse_onchip<R, 256, 1>), dim3(1), dim3(256), 0, stream, a);
+    else if (n <= 1024)
+        hipLaunchKernelGGL((k_coarse_onchip<R, 1024, 1>), dim3(1), dim3(1024), 0, stream, a);
+    else
+        hipLaunchKernelGGL((k_coarse_onchip<R, 1024, 2>), dim3(1), dim3(1024), 0, stream, a);
     LBM_HIP(hipGetLastError());
     return LBM_OK;
 }
@@ -409,7 +403,7 @@ extern "C" lbm_status lbm_coarse_params(const lbm_params *fine, int32_t r, lbm_p
 extern "C" size_t lbm_coarse_workspace_bytes(int32_t ncx, int32_t ncy)
 {
     if (ncx < 1 || ncy < 1) return 0;
-    return coarse_layout(ncx, ncy, true, false).total;
+    return coarse_layout(ncx, ncy, true).total;
 }
 
 extern "C" lbm_status lbm_coarse_solve(const lbm_params *fine, int32_t r, const double *d_keff, int32_t keff_mode,
@@ -429,8 +423,8 @@ extern "C" lbm_status lbm_coarse_solve(const lbm_params *fine, int32_t r, const 
     if (!(tol >= 0.0)) return set_error(LBM_EINVAL, fn + "tol must be >= 0");
     const int ncx = pc.nx, ncy = pc.ny, n = ncx * ncy;
     const bool f64 = fine->pop_dtype == LBM_F64;
-    const CoarseLayout L = coarse_layout(ncx, ncy, f64, true);
-    const size_t need = coarse_layout(ncx, ncy, true, false).total;
+    const CoarseLayout L = coarse_layout(ncx, ncy, f64);
+    const size_t need = L.total;
     if (!d_ws || ((uintptr_t)d_ws % kAlign) != 0 || ws_bytes < need)
         return set_error(LBM_EWORKSPACE, fn + "workspace NULL, misaligned or smaller than " + std::to_string(need));
     char *ws = static_cast<char *>(d_ws);
@@ -438,42 +432,62 @@ extern "C" lbm_status lbm_coarse_solve(const lbm_params *fine, int32_t r, const 
     int *flag = reinterpret_cast<int *>(ws + L.off_flag);
     double *perm_c = reinterpret_cast<double *>(ws + L.off_perm);
     double *force_c = reinterpret_cast<double *>(ws + L.off_force);
+    pc.perm_kind = LBM_PERM_TENSOR;
+    pc.pop_dtype = f64 ? LBM_F64 : LBM_F32_SHIFTED;
     hipLaunchKernelGGL(k_zero_i32c, dim3(1), dim3(1), 0, stream, flag);
     const int tensor = keff_mode == LBM_KEFF_TENSOR ? 1 : 0;
     const dim3 cg((n + 255) / 256), cb(256);
+    // the coefficients go where the path that uses them reads them
+    char *coef = ws + L.off_M, *heg = ws + L.off_heg;
+    if (L.field && !L.one_group) fine_coef_planes(pc, ws + L.off_fine, &coef, &heg);
+    double *pp = L.field ? nullptr : perm_c, *fp = L.field ? nullptr : force_c;
     if (f64)
         hipLaunchKernelGGL(k_coarse_coef<double>, cg, cb, 0, stream, d_keff, d_force, n, tensor, (double)r, pc.eps, pc.nu,
-                           fine->gx, fine->gy, reinterpret_cast<double *>(ws + L.off_M),
-                           reinterpret_cast<double *>(ws + L.off_heg), L.onchip ? nullptr : perm_c,
-                           L.onchip ? nullptr : force_c, flag);
+                           fine->gx, fine->gy, reinterpret_cast<double *>(coef), reinterpret_cast<double *>(heg), pp, fp,
+                           flag);
     else
         hipLaunchKernelGGL(k_coarse_coef<float>, cg, cb, 0, stream, d_keff, d_force, n, tensor, (double)r, pc.eps, pc.nu,
-                           fine->gx, fine->gy, reinterpret_cast<float *>(ws + L.off_M),
-                           reinterpret_cast<float *>(ws + L.off_heg), L.onchip ? nullptr : perm_c,
-                           L.onchip ? nullptr : force_c, flag);
+                           fine->gx, fine->gy, reinterpret_cast<float *>(coef), reinterpret_cast<float *>(heg), pp, fp,
+                           flag);
     LBM_HIP(hipGetLastError());
+
+    const int64_t ms = std::min<int64_t>((max_steps + check_every - 1) / check_every * check_every, (int64_t)1 << 30);
+    long long result[2] = {0, 0};
     int bad = 0;
+    if (L.one_group) {
+        // the permeability check is read back with the result: with a bad one the kernel leaves at once
+        const lbm_status ls = f64 ? launch_onchip<double>(pc, ws, L, tol, check_every, ms, d_u, d_rho, stream)
+                                  : launch_onchip<float>(pc, ws, L, tol, check_every, ms, d_u, d_rho, stream);
+        if (ls != LBM_OK) return ls;
+        LBM_HIP(hipMemcpyAsync(result, status, sizeof(result), hipMemcpyDeviceToHost, stream));
+    }
     LBM_HIP(hipMemcpyAsync(&bad, flag, sizeof(int), hipMemcpyDeviceToHost, stream));
     LBM_HIP(hipStreamSynchronize(stream));
     if (bad) return set_error(LBM_EINVAL, fn + "effective permeability must be positive definite");
-
-    if (L.onchip) {
-        const int64_t ms = (max_steps + check_every - 1) / check_every * check_every;
-        lbm_status ls = f64 ? launch_onchip<double, kCPT64>(pc, ws, L, tol, check_every, ms, d_u, d_rho, stream)
-                            : launch_onchip<float, kCPT32>(pc, ws, L, tol, check_every, ms, d_u, d_rho, stream);
-        if (ls != LBM_OK) return ls;
-        long long hs[2] = {0, 0};
-        LBM_HIP(hipMemcpyAsync(hs, status, sizeof(hs), hipMemcpyDeviceToHost, stream));
-        LBM_HIP(hipStreamSynchronize(stream));
-        if (steps_done) *steps_done = hs[0];
-        if (hs[1] == 2) return set_error(LBM_ENONFINITE, fn + "non-finite velocity");
-        if (hs[1] == 1) return set_error(LBM_ENOTCONV, fn + "tolerance not reached within max_steps");
+    if (L.field) {
+        if (!L.one_group) {
+            FieldRun f{};
+            f.p = pc;
+            f.p.rho0 = 1.0;  // as the one-group kernel: deviations from 1
+            f.ws = ws + L.off_fine;
+            f.prev = ws + L.off_perm;
+            f.status = status;
+            f.tol = tol;
+            f.check_every = check_every;
+            f.max_steps = ms;
+            f.u = d_u;
+            f.rho = d_rho;
+            f.stream = stream;
+            const lbm_status ls = run_to_steady_field(f, result);
+            if (ls != LBM_OK) return ls;
+        }
+        if (steps_done) *steps_done = result[0];
+        if (result[1] == 2) return set_error(LBM_ENONFINITE, fn + "non-finite velocity");
+        if (result[1] == 1) return set_error(LBM_ENOTCONV, fn + "tolerance not reached within max_steps");
         return LBM_OK;
     }
 
-    // HBM path: the fine-grid solver with the coarse tensor permeability
-    pc.perm_kind = LBM_PERM_TENSOR;
-    pc.pop_dtype = f64 ? LBM_F64 : LBM_F32_SHIFTED;
+    // the fine-grid solver with the coarse tensor permeability
     lbm_handle *h = nullptr;
     s = lbm_init(&h, &pc, perm_c, force_c, ws + L.off_fine, L.fine_bytes, stream);
     if (s != LBM_OK) return s;

@@ -983,6 +983,97 @@ __global__ __launch_bounds__(kBlock) void k_init(const double *__restrict__ perm
     for (int q = 0; q < 9; ++q) pops[(size_t)q * stride + c] = (R)0;
 }
 
+// Rest state (zero deviations) of n cells.
+template <typename R>
+__global__ __launch_bounds__(kBlock) void k_rest(R *__restrict__ pops, int stride, int n)
+{
+    const int c = blockIdx.x * kBlock + threadIdx.x;
+    if (c >= n) return;
+#pragma unroll
+    for (int q = 0; q < 9; ++q) pops[(size_t)q * stride + c] = (R)0;
+}
+
+// Convergence of the whole velocity field (the coarse solve's test), taken on
+// the device: the fields of the current state, the relative L2 change of the
+// velocity since the last check (kept rounded to R), and, in the workgroup
+// that finishes last, the decision. status: [0] steps, [1] flag, [2] the run
+// has ended, [3] workgroups that are done; host mirrors [0..2]. Once the run has ended later checks leave everything as
+// it is, so steps may be queued past the end of the run before it is known.
+template <typename R>
+__global__ __launch_bounds__(kBlock) void k_field_check(StepArgs<R> a, long long steps, bool first, double tol,
+                                                        long long max_steps, R *__restrict__ prev,
+                                                        double *__restrict__ partials, double *__restrict__ u_out,
+                                                        double *__restrict__ rho_out, long long *__restrict__ status,
+                                                        long long *__restrict__ host)
+{
+    __shared__ double red[2][kBlock / 64];
+    __shared__ bool last;
+    const int N = a.nx * a.ny, c = blockIdx.x * kBlock + threadIdx.x;
+    if (!first && status[2] != 0) return;
+    double d2 = 0.0, u2 = 0.0;
+    if (c < N) {
+        R fr[9];
+        pull<R, false>(a.fin, a.stride, a.nx, a.ny, c % a.nx, c / a.nx, fr);
+        double f[9];
+#pragma unroll
+        for (int i = 0; i < 9; ++i) f[i] = (double)fr[i];
+        double dr, jx, jy;
+        moments(f, dr, jx, jy);
+        const double rho = a.rho0_d + dr;
+        const double hx = jx + (double)a.hforce[c] * rho, hy = jy + (double)a.hforce[a.cstride + c] * rho;
+        const double e00 = a.coef[c], e01 = a.coef[a.cstride + c];
+        const double e10 = a.coef[2 * a.cstride + c], e11 = a.coef[3 * a.cstride + c];
+        const double ux = ((hx - e00 * hx) - e01 * hy) / rho, uy = ((hy - e11 * hy) - e10 * hx) / rho;
+        const R rx = (R)ux, ry = (R)uy;
+        const double dx = first ? 0.0 : (double)rx - (double)prev[c], dy = first ? 0.0 : (double)ry - (double)prev[N + c];
+        d2 = dx * dx + dy * dy;
+        u2 = ux * ux + uy * uy;
+        prev[c] = rx;
+        prev[N + c] = ry;
+        u_out[c] = ux;
+        u_out[N + c] = uy;
+        if (rho_out) rho_out[c] = rho;
+    }
+    d2 = wave_sum(d2);
+    u2 = wave_sum(u2);
+    if ((threadIdx.x & 63) == 0) {
+        red[0][threadIdx.x >> 6] = d2;
+        red[1][threadIdx.x >> 6] = u2;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        double sd = 0.0, su = 0.0;
+        for (int w = 0; w < kBlock / 64; ++w) {
+            sd += red[0][w];
+            su += red[1][w];
+        }
+        // device-wide visible before the count says so
+        __hip_atomic_store(&partials[2 * blockIdx.x], sd, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&partials[2 * blockIdx.x + 1], su, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const unsigned long long done = __hip_atomic_fetch_add(reinterpret_cast<unsigned long long *>(&status[3]), 1ull,
+                                                               __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+        last = done == gridDim.x - 1;
+    }
+    __syncthreads();
+    if (!last || threadIdx.x != 0) return;
+    double td = 0.0, tu = 0.0;
+    for (unsigned b = 0; b < gridDim.x; ++b) {
+        td += __hip_atomic_load(&partials[2 * b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        tu += __hip_atomic_load(&partials[2 * b + 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    long long flag = -1;
+    if (!isfinite(td) || !isfinite(tu)) flag = 2;
+    else if (!first && tol > 0.0 && sqrt(td) <= tol * sqrt(tu)) flag = 0;
+    else if (steps >= max_steps) flag = tol > 0.0 ? 1 : 0;
+    status[0] = steps;
+    status[1] = flag;
+    status[2] = flag >= 0;
+    status[3] = 0;
+    host[0] = steps;
+    host[1] = flag;
+    host[2] = flag >= 0;
+}
+
 // Full pre-collision populations of the current state, FP64 [9][ny][nx].
 template <typename R, bool WALLS>
 __global__ __launch_bounds__(kBlock) void k_get_pops(const R *__restrict__ fin, int stride, int nx,
@@ -1273,11 +1364,10 @@ struct StepDFn {
 // them: 64^2 FP32 state D = 10 6.9 us (measured 7.0), 400^2 FP64 with a force
 // D = 8 14.3 (14.8), 700^2 FP32 D = 8 22.1 (22.4), 1000^2 FP32 arithmetic D = 7
 // 24.6 (24.4), 2048^2 FP64 D = 6 179 (184).
-double launch_us(const lbm_params &p, bool force, int shape, int D, int tx, int ty)
+double launch_us(const lbm_params &p, bool force, int cus, int shape, int D, int tx, int ty)
 {
     const bool f64 = p.pop_dtype == LBM_F64, fast = p.pop_dtype == LBM_F32_FAST;
     const double nt = (double)((p.nx + tx - 1) / tx) * ((p.ny + ty - 1) / ty);
-    const double cus = std::max(1, device_cu_count());
     const int ax = tx + 2 * (D - 1), ay = ty + 2 * (D - 1);
     const bool two = shape == kRows768 || shape == kRows1024 || shape == kTile32;
     const double r = (two && nt > cus) ? 2.0 : 1.0;  // tiles of a CU at once
@@ -1306,17 +1396,20 @@ Plan plan_launches(const lbm_params &p, bool force)
 {
     Plan pl{};
     const bool f64 = p.pop_dtype == LBM_F64, fast = p.pop_dtype == LBM_F32_FAST;
+    const int cus = std::max(1, device_cu_count());
     for (int D = 2; D <= kMaxDepth; ++D) {
         Launch best{kTile1024, 1, 1, 1e30};
         auto offer = [&](int shape, int tx, int ty) {
-            const double us = launch_us(p, force, shape, D, tx, ty);
+            const double us = launch_us(p, force, cus, shape, D, tx, ty);
             if (us < best.us) best = Launch{shape, tx, ty, us};
         };
         const int h2 = 2 * (D - 1);
         const int cap[3] = {512, 1024, 2048}, shape[3] = {kTile512, kTile1024, kTile2048};
         for (int i = 0; i < 3; ++i)
-            for (int w = 4; w <= 64 && w + h2 <= cap[i]; ++w) {
+            for (int w = 4, last = 0; w <= 64 && w + h2 <= cap[i]; ++w) {
                 const int tx = (p.nx + (p.nx + w - 1) / w - 1) / ((p.nx + w - 1) / w);  // even columns of tiles
+                if (tx == last) continue;
+                last = tx;
                 const int room = cap[i] / (tx + h2) - h2;
                 if (room < 1) break;
                 const int nty = (p.ny + room - 1) / room;
@@ -1372,7 +1465,94 @@ lbm_status mean_velocity(lbm_handle *h, double out[2])
     return LBM_OK;
 }
 
+// Queue the steps of one stretch until at least `least` of them are queued.
+int64_t queue_steps(lbm_handle *h, int64_t stretch, int64_t least)
+{
+    int64_t n = 0;
+    while (n < std::min(stretch, least)) {
+        const int d = launch_depth(h, stretch - n);
+        if (d >= 2)
+            dispatch<StepDFn>(h, d);
+        else
+            dispatch<StepFn>(h);
+        h->cur ^= 1;
+        n += d;
+    }
+    return n;
+}
+
+template <typename R>
+void field_check(const lbm_handle &h, const FieldRun &f, int64_t steps, bool first, long long *host)
+{
+    const int n = h.p.nx * h.p.ny;
+    hipLaunchKernelGGL(k_field_check<R>, dim3((n + kBlock - 1) / kBlock), dim3(kBlock), 0, h.stream, step_args<R>(&h),
+                       (long long)steps, first, f.tol, (long long)f.max_steps, reinterpret_cast<R *>(f.prev),
+                       reinterpret_cast<double *>(h.ws + h.L.off_part), f.u, f.rho, f.status, host);
+}
+
 }  // namespace
+
+void fine_coef_planes(const lbm_params &p, char *ws, char **coef, char **force)
+{
+    const Layout L = layout_of(&p);
+    *coef = ws + L.off_coef;
+    *force = ws + L.off_force;
+}
+
+// The steps of the next check interval are queued (up to kAhead of them) before
+// the host waits for the result of the last check, so the device does not idle
+// while the host reads it.
+lbm_status run_to_steady_field(const FieldRun &f, long long result[2])
+{
+    constexpr int64_t kAhead = 64;
+    lbm_handle h{};
+    h.p = f.p;
+    h.L = layout_of(&f.p);
+    h.stream = f.stream;
+    h.ws = f.ws;
+    h.has_force = true;
+    h.plan = plan_launches(h.p, true);
+    const bool f64 = h.p.pop_dtype == LBM_F64;
+    long long *host = nullptr;
+    hipEvent_t ev = nullptr;
+    LBM_HIP(hipHostMalloc((void **)&host, 4 * sizeof(long long), hipHostMallocDefault));
+    host[0] = host[1] = host[2] = 0;
+    hipError_t e = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
+    if (e == hipSuccess) {
+        const int n = h.p.nx * h.p.ny, nb = (n + kBlock - 1) / kBlock;
+        hipLaunchKernelGGL(k_zero_i32, dim3(1), dim3(64), 0, f.stream, reinterpret_cast<int *>(f.status), 8);
+        if (f64)
+            hipLaunchKernelGGL(k_rest<double>, dim3(nb), dim3(kBlock), 0, f.stream,
+                               reinterpret_cast<double *>(h.ws + h.L.off_a), (int)h.L.stride, n);
+        else
+            hipLaunchKernelGGL(k_rest<float>, dim3(nb), dim3(kBlock), 0, f.stream,
+                               reinterpret_cast<float *>(h.ws + h.L.off_a), (int)h.L.stride, n);
+        int64_t steps = 0, ahead = 0;  // ahead: steps of the current interval already queued
+        while (e == hipSuccess) {
+            queue_steps(&h, f.check_every - ahead, f.check_every);
+            steps += f.check_every;
+            if (f64)
+                field_check<double>(h, f, steps, steps == f.check_every, host);
+            else
+                field_check<float>(h, f, steps, steps == f.check_every, host);
+            e = hipGetLastError();
+            if (e == hipSuccess) e = hipEventRecord(ev, f.stream);
+            ahead = steps < f.max_steps ? queue_steps(&h, f.check_every, kAhead) : 0;
+            if (e == hipSuccess) e = hipGetLastError();
+            if (e == hipSuccess) e = hipEventSynchronize(ev);
+            if (e != hipSuccess || host[2] != 0) break;
+        }
+    }
+    // what was queued ahead uses the workspace and the host's mirror
+    const hipError_t es = hipStreamSynchronize(f.stream);
+    if (e == hipSuccess) e = es;
+    result[0] = host[0];
+    result[1] = host[1];
+    if (ev) (void)hipEventDestroy(ev);
+    (void)hipHostFree(host);
+    return e == hipSuccess ? LBM_OK : hip_check(e, "lbm_coarse_solve");
+}
+
 }  // namespace lbm
 
 using namespace lbm;

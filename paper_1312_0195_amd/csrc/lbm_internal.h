@@ -58,4 +58,25 @@ __device__ inline double wave_sum(double v)
     return v;
 }
 
+// A periodic lattice with a tensor drag and a force per cell, run from rest until
+// its velocity field changes by no more than tol (relative, L2) between checks
+// (the middle range of the coarse solve, in lbm_fine.hip).
+struct FieldRun {
+    lbm_params p;
+    char *ws;              // a fine-grid workspace for p, its coefficient planes filled
+    void *prev;            // 2 n values of the population type
+    long long *status;     // 4 device values
+    double tol;
+    int check_every;
+    int64_t max_steps;     // a multiple of check_every
+    double *u, *rho;       // [2][n], [n] or null
+    hipStream_t stream;
+};
+
+// Where a fine-grid workspace for p holds its coefficient and force planes.
+void fine_coef_planes(const lbm_params &p, char *ws, char **coef, char **force);
+
+// result: steps and flag (0 converged or no tolerance, 1 step cap, 2 non-finite).
+lbm_status run_to_steady_field(const FieldRun &f, long long result[2]);
+
 }  // namespace lbm

@@ -1,0 +1,70 @@
+"""GPU: the coarse solve at the edges of its size ranges, against the fine-grid
+solver on the same lattice: its field after the reported steps, and the
+convergence test between the last checks."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def L():
+    from paper_1312_0195_amd import lbm
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    lbm.lib()
+    return lbm
+
+
+@pytest.mark.parametrize("dtype", [0, 1])
+@pytest.mark.parametrize("ncx,ncy", [(1, 2), (16, 16), (257, 1), (32, 32), (25, 41), (64, 26), (37, 45), (64, 32),
+                                     (64, 64)])
+def test_matches_fine_solver_and_its_own_test(L, ncx, ncy, dtype):
+    if dtype == 1 and ncx * ncy > 2048:
+        pytest.skip("larger FP64 grids are a fine-grid solve themselves")
+    r, tol, every = 16, 1e-5, 50
+    rng = np.random.default_rng(ncx * 100 + ncy)
+    k = np.exp(0.6 * rng.standard_normal((ncy, ncx)))
+    K = np.stack([k, 0.2 * k, 0.1 * k, 0.5 + k[::-1, ::-1]], axis=-1)
+    G = 1e-6 * (1.0 + 0.5 * rng.standard_normal((ncy, ncx, 2)))
+    fine = L.make_params(ncx * r, ncy * r, 0.8, 0.4, 0.1, 1.0, 0.0, 0.0, 0, dtype)
+    u = torch.empty((2, ncy, ncx), dtype=torch.float64, device="cuda")
+    rho = torch.empty_like(u[0])
+    nb = L.lbm_coarse_workspace_bytes(ncx, ncy)
+    ws = torch.empty(nb, dtype=torch.uint8, device="cuda")
+    st, steps = L.lbm_coarse_solve(fine, r, torch.as_tensor(K).cuda(), L.LBM_KEFF_TENSOR, torch.as_tensor(G).cuda(),
+                                   20000, tol, every, u, rho, ws, nb)
+    assert st == L.LBM_OK and steps % every == 0 and steps >= 2 * every
+    pc = L.lbm_coarse_params(fine, r)
+    pc.perm_kind = L.LBM_PERM_TENSOR
+    s = L.FineSolver(pc, K / (r * r), r * G)
+    fields = {}
+    done = 0
+    for n in (steps - 2 * every, steps - every, steps):
+        s.step(n - done, mean=False)
+        done = n
+        fields[n] = s.fields()
+    ref, rref = fields[steps]
+    # the same steps in the same arithmetic: the coefficients may differ by a rounding of the state type
+    bound = 1e-5 if dtype == 0 else 1e-11
+    assert float((u - ref).abs().max()) <= bound * float(ref.abs().max())
+    assert float((rho - rref).abs().max()) <= bound * float(ref.abs().max())
+    change = [float((fields[b][0] - fields[a][0]).norm() / fields[b][0].norm())
+              for a, b in ((steps - 2 * every, steps - every), (steps - every, steps))]
+    assert change[1] <= tol * 1.001
+    if steps > 2 * every:
+        assert change[0] > tol * 0.999
+    s.close()
+
+
+def test_bad_permeability_is_refused_in_every_range(L):
+    for n, dtype in ((8, 0), (50, 0), (64, 0), (70, 0), (30, 1), (44, 1)):
+        fine = L.make_params(n * 8, n * 8, 0.8, 0.4, 0.1, 1.0, 1e-6, 0.0, 0, dtype)
+        K = np.tile(np.array([1.0, 0.0, 0.0, 1.0]), (n, n, 1))
+        K[n // 2, 1, 0] = -1.0
+        u = torch.empty((2, n, n), dtype=torch.float64, device="cuda")
+        nb = L.lbm_coarse_workspace_bytes(n, n)
+        ws = torch.empty(nb, dtype=torch.uint8, device="cuda")
+        with pytest.raises(L.LbmError) as e:
+            L.lbm_coarse_solve(fine, 8, torch.as_tensor(K).cuda(), 1, None, 130, 1e-6, 50, u, None, ws, nb)
+        assert e.value.status == L.LBM_EINVAL
