@@ -53,6 +53,7 @@
 #include <mutex>
 #include <numeric>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "lbm_internal.h"
@@ -154,8 +155,8 @@ __device__ inline Consts<double>::Consts(const LocalArgs &a)
 //   rho u_eq - U = 2 tau D (U + j' + rho eps G / 2) + (1 - 2 tau)(U + j') - U
 //               = j' + 2 tau (rho eps G / 2 - E (U + j' + rho eps G / 2)),
 // every term of which is as small as the non-uniform flow or the drag.
-// FP64 items take cE = 2 tau E per cell and tgx, tgy = 2 tau eps G / 2 of
-// the item's drive; FP32 items take cE = 2 E, tgx, tgy = 2 eps G / 2 and
+// FP64 items take cE = 2 tau E per cell and tg = 2 tau eps G / 2 along the
+// item's drive; FP32 items take cE = 2 E, tg = 2 eps G / 2 and
 // form om (rho u_eq - U) as om j' + 2 (rho eps G / 2 - E (...)), with the
 // exact factor 2 = om 2 tau,
 // and weights that sum exactly (the rest weight and the diagonal momentum
@@ -163,9 +164,11 @@ __device__ inline Consts<double>::Consts(const LocalArgs &a)
 // as a product of two rounded constants, every step would add a fixed
 // fraction (~3e-8) of the mass and momentum terms, a bias the slow relaxation
 // of a permeable patch accumulates. Ux, Uy: the reference U.
-template <typename P>
-__device__ __forceinline__ void collide(P f[9], P cE, P hegx, P hegy, P tgx, P tgy, P Ux, P Uy,
-                                        const Consts<P> &k)
+// DRIVE 0: the item's drive is along x (hegy = tgy = 0), 1: along y; the terms of
+// the other component that the zeros make trivial are left out (the same
+// values, but for the sign of a zero): two operations of 55.
+template <int DRIVE, typename P>
+__device__ __forceinline__ void collide(P f[9], P cE, P heg, P tg, P Ux, P Uy, const Consts<P> &k)
 {
     const P dr = ((f[0] + f[1]) + (f[2] + f[3])) + ((f[4] + f[5]) + (f[6] + f[7])) + f[8];
     const P jx = (f[1] - f[3]) + ((f[5] - f[6]) + (f[8] - f[7]));
@@ -173,8 +176,8 @@ __device__ __forceinline__ void collide(P f[9], P cE, P hegx, P hegy, P tgx, P t
     const P rho = P(1) + dr;
     const P om = k.om, omc = k.omc;
     if constexpr (sizeof(P) == 8) {
-        const P mx = (jx + tgx * rho) - cE * (jx + (hegx * rho + Ux));
-        const P my = (jy + tgy * rho) - cE * (jy + (hegy * rho + Uy));
+        const P mx = DRIVE == 0 ? (jx + tg * rho) - cE * (jx + (heg * rho + Ux)) : jx - cE * (jx + Ux);
+        const P my = DRIVE == 1 ? (jy + tg * rho) - cE * (jy + (heg * rho + Uy)) : jy - cE * (jy + Uy);
         const P s0 = (P(4) / P(9)) * om * dr;
         const P b = (P(1) / P(9)) * om * dr;
         const P bx = (P(1) / P(3)) * om * mx;
@@ -196,10 +199,10 @@ __device__ __forceinline__ void collide(P f[9], P cE, P hegx, P hegy, P tgx, P t
         // every fused multiply-add written out and no other contraction, so
         // the launches compiled for 1, 2 or 4 cells per thread round alike
 #pragma clang fp contract(off)
-        // cE = 2 E, tgx = 2 eps G / 2 here (doublings are exact), so
+        // cE = 2 E, tg = 2 eps G / 2 here (doublings are exact), so
         // t = 2 (rho eps G / 2 - E (j' + rho eps G / 2 + U)) in one rounding
-        const P tx = __builtin_fmaf(-cE, jx + __builtin_fmaf(hegx, rho, Ux), tgx * rho);
-        const P ty = __builtin_fmaf(-cE, jy + __builtin_fmaf(hegy, rho, Uy), tgy * rho);
+        const P tx = DRIVE == 0 ? __builtin_fmaf(-cE, jx + __builtin_fmaf(heg, rho, Ux), tg * rho) : -cE * (jx + Ux);
+        const P ty = DRIVE == 1 ? __builtin_fmaf(-cE, jy + __builtin_fmaf(heg, rho, Uy), tg * rho) : -cE * (jy + Uy);
         const P Mx = __builtin_fmaf(om, jx, tx), My = __builtin_fmaf(om, jy, ty);
         const P D = om * dr;
         const P b = D * (P(1) / P(9));
@@ -223,12 +226,27 @@ __device__ __forceinline__ void collide(P f[9], P cE, P hegx, P hegy, P tgx, P t
     }
 }
 
+// Cells between the planes of an item (0: the item's own cells).
+constexpr int local_plane(int T, size_t elem, int cpt) { return T == 1024 && elem == 4 ? T * cpt : 0; }
+
 // CPT: the most cells any thread of this launch owns (1, 2 or 4); the
 // register arrays are sized by it, so launches of small patches keep fewer
 // registers live and fit more workgroups per CU.
+//
+// Bound by the VALU: a step of a cell is 53 FP32 operations and, with the
+// parity of the step and the planes' offsets known at compile time, one or two
+// more instructions (58 to 62 before). Measured: 4096 tiles of 32 x 32 18.0 ->
+// 16.7 ms, 4096 mixed sides 16..64 39.7 -> 38.0 ms, 8 patches of 64 x 64 (one
+// item per CU, four cells per thread) 1.82 -> 1.81 us per step. Reading a
+// thread's next cell before colliding the last was slower (mixed sides
+// 40.1 ms).
 template <int T, typename P, int CPT>
 __global__ __launch_bounds__(T, (CPT == 1 && sizeof(P) == 4 ? 8 : 1)) void k_local(LocalArgs a)
 {
+    // distance of an item's planes: fixed for the FP32 launches on 1024
+    // threads, which hold one or two workgroups per CU whatever their LDS
+    // (LDS offsets are then immediate); else packed by the item's own cells
+    constexpr int PS = local_plane(T, sizeof(P), CPT);
     extern __shared__ __align__(16) unsigned char lds_raw[];
     P *lds = reinterpret_cast<P *>(lds_raw);
     const Consts<P> kc(a);
@@ -247,7 +265,8 @@ __global__ __launch_bounds__(T, (CPT == 1 && sizeof(P) == 4 ? 8 : 1)) void k_loc
     double prev_x = 0.0, prev_y = 0.0;
     int out = 0, x0 = 0, y0 = 0;
     int item_side = 0;  // side of the slot's item (classes of merged sides)
-    P hegx = 0, hegy = 0, tgx = 0, tgy = 0;
+    int drive = 0;
+    const P heg = kc.heg, tg = (P)((sizeof(P) == 8 ? a.twotau_d : 2.0) * a.heg_d);
     P Ux = 0, Uy = 0;  // reference momentum of the rebased state
     double hegx_d = 0.0, hegy_d = 0.0;
     // per-cell registers
@@ -266,7 +285,8 @@ __global__ __launch_bounds__(T, (CPT == 1 && sizeof(P) == 4 ? 8 : 1)) void k_loc
         int S2 = S * S;
         const int slot = tid / G, lt = tid - slot * G;
         const bool in_slot = slot < cd.nslots;
-        P *A = lds + (size_t)(in_slot ? slot : 0) * 8 * S2;
+        P *A = lds + (size_t)(in_slot ? slot : 0) * (PS ? G * CPT : 8 * S2);
+        int Q = PS ? PS : S2;  // plane distance
 
         // ---- control: claim items for slots that need one -------------------
         if (in_slot && lt == 0 && need_item) {
@@ -286,14 +306,11 @@ __global__ __launch_bounds__(T, (CPT == 1 && sizeof(P) == 4 ? 8 : 1)) void k_loc
                 if (cd.merged) {
                     S = it.z;
                     S2 = S * S;
+                    if (!PS) Q = S2;
                 }
-                const int drive = out & 1;
-                hegx = drive == 0 ? kc.heg : P(0);
-                hegy = drive == 1 ? kc.heg : P(0);
+                drive = out & 1;
                 hegx_d = drive == 0 ? a.heg_d : 0.0;
                 hegy_d = drive == 1 ? a.heg_d : 0.0;
-                tgx = (P)((sizeof(P) == 8 ? a.twotau_d : 2.0) * hegx_d);
-                tgy = (P)((sizeof(P) == 8 ? a.twotau_d : 2.0) * hegy_d);
                 Ux = Uy = P(0);
                 steps = 0;
                 have_prev = false;
@@ -311,7 +328,7 @@ __global__ __launch_bounds__(T, (CPT == 1 && sizeof(P) == 4 ? 8 : 1)) void k_loc
                                             : (P)__longlong_as_double(0x7ff8000000000000LL);
                         f0[k] = P(0);
 #pragma unroll
-                        for (int q = 0; q < 8; ++q) A[q * S2 + c] = P(0);
+                        for (int q = 0; q < 8; ++q) A[q * Q + c] = P(0);
                     }
                 }
             }
@@ -330,57 +347,80 @@ __global__ __launch_bounds__(T, (CPT == 1 && sizeof(P) == 4 ? 8 : 1)) void k_loc
 
         // ---- check_every steps ----------------------------------------------
         const bool active = in_slot && item >= 0;
-        for (int st = 0; st < a.check_every; ++st) {
-            if (active) {
-                const bool odd = ((steps + st) & 1) != 0;
+        // (even, so an even step is followed by an odd one within the loop; a
+        // slot's waves share its drive)
+        const bool along_y = __builtin_amdgcn_readfirstlane(drive) != 0;
+        auto even_step = [&](auto dr) {  // own slots, in order; written back reversed
 #pragma unroll
-                for (int k = 0; k < CPT; ++k) {
-                    const int c = lt + k * G;
-                    if (k < C && c < S2) {
-                        const int x = xy[k] & 255, y = xy[k] >> 8;
-                        P f[9];
-                        f[0] = f0[k];
-                        if (!odd) {
-                            // own slots, in order; written back reversed
+            for (int k = 0; k < CPT; ++k) {
+                const int c = lt + k * G;
+                if (k < C && c < S2) {
+                    P f[9];
+                    f[0] = f0[k];
 #pragma unroll
-                            for (int q = 1; q < 9; ++q) f[q] = A[(q - 1) * S2 + c];
-                            collide<P>(f, tE[k], hegx, hegy, tgx, tgy, Ux, Uy, kc);
-                            A[(3 - 1) * S2 + c] = f[1];
-                            A[(4 - 1) * S2 + c] = f[2];
-                            A[(1 - 1) * S2 + c] = f[3];
-                            A[(2 - 1) * S2 + c] = f[4];
-                            A[(7 - 1) * S2 + c] = f[5];
-                            A[(8 - 1) * S2 + c] = f[6];
-                            A[(5 - 1) * S2 + c] = f[7];
-                            A[(6 - 1) * S2 + c] = f[8];
-                        } else {
-                            const int xm = x == 0 ? S - 1 : x - 1, xp = x == S - 1 ? 0 : x + 1;
-                            const int rm = (y == 0 ? S - 1 : y - 1) * S, rp = (y == S - 1 ? 0 : y + 1) * S;
-                            const int r0 = y * S;
-                            // f_a(x) = A[opp a][x - e_a]
-                            f[1] = A[(3 - 1) * S2 + r0 + xm];
-                            f[2] = A[(4 - 1) * S2 + rm + x];
-                            f[3] = A[(1 - 1) * S2 + r0 + xp];
-                            f[4] = A[(2 - 1) * S2 + rp + x];
-                            f[5] = A[(7 - 1) * S2 + rm + xm];
-                            f[6] = A[(8 - 1) * S2 + rm + xp];
-                            f[7] = A[(5 - 1) * S2 + rp + xp];
-                            f[8] = A[(6 - 1) * S2 + rp + xm];
-                            collide<P>(f, tE[k], hegx, hegy, tgx, tgy, Ux, Uy, kc);
-                            // f*_a goes to A[a][x + e_a]
-                            A[(1 - 1) * S2 + r0 + xp] = f[1];
-                            A[(2 - 1) * S2 + rp + x] = f[2];
-                            A[(3 - 1) * S2 + r0 + xm] = f[3];
-                            A[(4 - 1) * S2 + rm + x] = f[4];
-                            A[(5 - 1) * S2 + rp + xp] = f[5];
-                            A[(6 - 1) * S2 + rp + xm] = f[6];
-                            A[(7 - 1) * S2 + rm + xm] = f[7];
-                            A[(8 - 1) * S2 + rm + xp] = f[8];
-                        }
-                        f0[k] = f[0];
-                    }
-                    __builtin_amdgcn_sched_barrier(0);  // one cell at a time: bounded register use
+                    for (int q = 1; q < 9; ++q) f[q] = A[(q - 1) * Q + c];
+                    collide<decltype(dr)::value, P>(f, tE[k], heg, tg, Ux, Uy, kc);
+                    A[(3 - 1) * Q + c] = f[1];
+                    A[(4 - 1) * Q + c] = f[2];
+                    A[(1 - 1) * Q + c] = f[3];
+                    A[(2 - 1) * Q + c] = f[4];
+                    A[(7 - 1) * Q + c] = f[5];
+                    A[(8 - 1) * Q + c] = f[6];
+                    A[(5 - 1) * Q + c] = f[7];
+                    A[(6 - 1) * Q + c] = f[8];
+                    f0[k] = f[0];
                 }
+                __builtin_amdgcn_sched_barrier(0);  // one cell at a time: bounded register use
+            }
+        };
+        auto odd_step = [&](auto dr) {
+#pragma unroll
+            for (int k = 0; k < CPT; ++k) {
+                const int c = lt + k * G;
+                if (k < C && c < S2) {
+                    const int x = xy[k] & 255, y = xy[k] >> 8;
+                    const int xm = x == 0 ? S - 1 : x - 1, xp = x == S - 1 ? 0 : x + 1;
+                    const int rm = (y == 0 ? S - 1 : y - 1) * S, rp = (y == S - 1 ? 0 : y + 1) * S;
+                    const int r0 = y * S;
+                    P f[9];
+                    f[0] = f0[k];
+                    // f_a(x) = A[opp a][x - e_a]
+                    f[1] = A[(3 - 1) * Q + r0 + xm];
+                    f[2] = A[(4 - 1) * Q + rm + x];
+                    f[3] = A[(1 - 1) * Q + r0 + xp];
+                    f[4] = A[(2 - 1) * Q + rp + x];
+                    f[5] = A[(7 - 1) * Q + rm + xm];
+                    f[6] = A[(8 - 1) * Q + rm + xp];
+                    f[7] = A[(5 - 1) * Q + rp + xp];
+                    f[8] = A[(6 - 1) * Q + rp + xm];
+                    collide<decltype(dr)::value, P>(f, tE[k], heg, tg, Ux, Uy, kc);
+                    // f*_a goes to A[a][x + e_a]
+                    A[(1 - 1) * Q + r0 + xp] = f[1];
+                    A[(2 - 1) * Q + rp + x] = f[2];
+                    A[(3 - 1) * Q + r0 + xm] = f[3];
+                    A[(4 - 1) * Q + rm + x] = f[4];
+                    A[(5 - 1) * Q + rp + xp] = f[5];
+                    A[(6 - 1) * Q + rp + xm] = f[6];
+                    A[(7 - 1) * Q + rm + xm] = f[7];
+                    A[(8 - 1) * Q + rm + xp] = f[8];
+                    f0[k] = f[0];
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        };
+        for (int st = 0; st < a.check_every; st += 2) {
+            if (active) {
+                if (along_y)
+                    even_step(std::integral_constant<int, 1>{});
+                else
+                    even_step(std::integral_constant<int, 0>{});
+            }
+            __syncthreads();
+            if (active) {
+                if (along_y)
+                    odd_step(std::integral_constant<int, 1>{});
+                else
+                    odd_step(std::integral_constant<int, 0>{});
             }
             __syncthreads();
         }
@@ -397,7 +437,7 @@ __global__ __launch_bounds__(T, (CPT == 1 && sizeof(P) == 4 ? 8 : 1)) void k_loc
                     double fd[9];
                     fd[0] = f0[k];
 #pragma unroll
-                    for (int q = 1; q < 9; ++q) fd[q] = (double)A[(q - 1) * S2 + c];
+                    for (int q = 1; q < 9; ++q) fd[q] = (double)A[(q - 1) * Q + c];
                     const double dr = ((fd[0] + fd[1]) + (fd[2] + fd[3])) + ((fd[4] + fd[5]) + (fd[6] + fd[7])) + fd[8];
                     const double jpx = (fd[1] - fd[3]) + ((fd[5] - fd[6]) + (fd[8] - fd[7]));
                     const double jpy = (fd[2] - fd[4]) + ((fd[5] + fd[6]) - (fd[7] + fd[8]));
@@ -492,14 +532,14 @@ __global__ __launch_bounds__(T, (CPT == 1 && sizeof(P) == 4 ? 8 : 1)) void k_loc
                     const int c = lt + k * G;
                     if (k < C && c < S2) {
                         // even order: A[a - 1][c] holds f'_a of cell c
-                        A[0 * S2 + c] -= ax;
-                        A[1 * S2 + c] -= ay;
-                        A[2 * S2 + c] += ax;
-                        A[3 * S2 + c] += ay;
-                        A[4 * S2 + c] -= dp;
-                        A[5 * S2 + c] += dm;
-                        A[6 * S2 + c] += dp;
-                        A[7 * S2 + c] -= dm;
+                        A[0 * Q + c] -= ax;
+                        A[1 * Q + c] -= ay;
+                        A[2 * Q + c] += ax;
+                        A[3 * Q + c] += ay;
+                        A[4 * Q + c] -= dp;
+                        A[5 * Q + c] += dm;
+                        A[6 * Q + c] += dp;
+                        A[7 * Q + c] -= dm;
                     }
                 }
             }
@@ -1038,6 +1078,7 @@ extern "C" lbm_status lbm_local_keff(const lbm_local_params *lp, int32_t n_patch
             lds = std::max(lds, (size_t)c.nslots * cb * c.side * c.side);
         }
         const int cpt = cmax <= 1 ? 1 : (cmax <= 2 ? 2 : 4);
+        if (const int ps = local_plane(T, f64 ? 8 : 4, cpt)) lds = 8 * sizeof(float) * (size_t)ps;
         const int grid = std::max(1, need);
         if (f64)
             return (T == 256) ? launch_local<256, double>(g, lds, grid, cpt, st, cu_budget)
