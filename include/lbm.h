@@ -441,7 +441,7 @@ size_t lbm3d_workspace_bytes(const lbm3d_params *p);
 lbm_status lbm3d_init(lbm3d_handle **h, const lbm3d_params *p, const double *d_kappa, void *d_ws,
                       size_t ws_bytes, hipStream_t stream);
 
-/* Advance up to max_steps steps, one launch per step. check_every, tol,
+/* Advance up to max_steps steps, one or two per launch. check_every, tol,
  * steps_done and mean_u (three components, FP64 volume average of the flow
  * velocity) behave as in lbm_step. */
 lbm_status lbm3d_step(lbm3d_handle *h, int64_t max_steps, double tol, int32_t check_every,

@@ -12,7 +12,8 @@
 // population from its upstream neighbour, collides in FP64 and stores, so
 // every population element is read once and written once per step:
 // 19 x 2 x 4 B + 4 B of drag coefficient = 156 B per lattice update (FP32).
-// With FP32 state two steps run per launch (k3_step2, below), halving that.
+// Two steps per launch (k3_step2, below) halve that; small grids, whose state
+// stays in the caches, take single steps (plan_steps).
 //
 // Population order (also the layout of lbm3d_get_populations): rest; +x, -x,
 // +y, -y, +z, -z; the diagonals of the xy plane (+x+y, -x-y, +x-y, -x+y), of
@@ -224,10 +225,10 @@ __global__ __launch_bounds__(kBlock3) void k3_step(Args3<R> a)
 }
 
 // ---------------------------------------------------------------------------
-// Two time steps per launch (FP32 state): each workgroup owns an IX x IY tile
+// Two time steps per launch: each workgroup owns an IX x IY tile
 // of (x, y) columns and a run of zc planes, and marches up z. For every
 // plane p it takes step 1 on the tile plus a one-cell halo, (IX + 2) x
-// (IY + 2) cells (pulled from HBM, collided in FP64, rounded to FP32 as a
+// (IY + 2) cells (pulled from HBM, collided in FP64, rounded to the state's type as a
 // stored step would be), into LDS, then step 2 on the IX x IY cells of plane
 // p - 1, pulling from the step-1 planes p - 2, p - 1 and p, and stores that
 // to HBM. The state passes through HBM once per two steps (156 B per two
@@ -242,14 +243,12 @@ __global__ __launch_bounds__(kBlock3) void k3_step(Args3<R> a)
 // step 2 and stay in flight across the barrier, which orders LDS operations
 // only.
 //
-// Tile 64 x 8 (66 x 10 with the halo: 29% extra step-1 cells), 512 threads,
-// 113.5 KB of LDS: one workgroup per CU. Measured on 256^3 against 32 x 8,
-// 30 x 6, 32 x 4, 64 x 4, 32 x 16, 62 x 6, 64 x 6, 96 x 4 and 128 x 4 tiles,
-// without the prefetch, and with z runs of 16 to 128 planes (all
-// bit-identical): 64 x 8 with runs of 128 planes was the fastest. The run
-// length zc is chosen per grid on the host (launch_step2).
+// Tiles and z runs are chosen per grid on the host (plan_steps): with FP32 state
+// 64 x 8 (29% extra step-1 cells, 113.5 KB of LDS: one workgroup per CU) or 16 x 8
+// (four per CU); with FP64 state 64 x 4 (136 KB, one) or 16 x 8 (two). Measured on 256^3 with FP32 state against 32 x 8, 30 x 6, 32 x 4, 32 x 16,
+// 62 x 6, 64 x 6, 96 x 4 and 128 x 4, without the prefetch, and with z runs of 16
+// to 128 planes: 64 x 8 with runs of 128 planes was the fastest.
 // ---------------------------------------------------------------------------
-constexpr int k2IX = 64, k2IY = 8, k2T = 512;
 
 // Barrier that orders LDS only: global loads in flight stay in flight.
 __device__ __forceinline__ void lds_barrier()
@@ -271,17 +270,15 @@ struct Tile2 {
     static_assert(IX * IY <= T, "one step-2 cell per thread");
     static_assert(R1 <= 2, "at most two step-1 cells per thread");
 };
-using Tl2 = Tile2<k2IX, k2IY, k2T>;
 
-template <bool WALLS>
-__global__ __launch_bounds__(k2T) void k3_step2(Args3<float> a, int zc)
+template <typename R, bool WALLS, int IX, int IY, int T>
+__global__ __launch_bounds__(T) void k3_step2(Args3<R> a, int zc)
 {
-    constexpr bool PF = true;
-    constexpr int IX = k2IX, IY = k2IY, T = k2T;
+    using Tl2 = Tile2<IX, IY, T>;
     constexpr int EX = Tl2::EX, NE = Tl2::NE, R1 = Tl2::R1;
-    __shared__ float sin_[2][9][NE];  // in-plane populations, planes p - 1, p
-    __shared__ float sup[3][5][NE];   // +z populations, planes p - 2 .. p
-    __shared__ float sdn[2][5][NE];   // -z populations, planes p - 1, p
+    __shared__ R sin_[2][9][NE];  // in-plane populations, planes p - 1, p
+    __shared__ R sup[3][5][NE];   // +z populations, planes p - 2 .. p
+    __shared__ R sdn[2][5][NE];   // -z populations, planes p - 1, p
     constexpr int kXcd = 8;
     const int nb = gridDim.x, bid = blockIdx.x;
     const int qq = nb / kXcd, rem = nb % kXcd;
@@ -315,15 +312,15 @@ __global__ __launch_bounds__(k2T) void k3_step2(Args3<float> a, int zc)
         return pz < 0 ? pz + a.nz : pz;
     };
     auto have1 = [&](int p) { return WALLS ? (p >= 0 && p < a.nz) : true; };
-    auto load1 = [&](int r, int pz, float fr[Q], float &D) {
-        pull3<float, WALLS>(a.fin, a.stride, a.nx, a.ny, a.nz, gx1[r], gy1[r], pz, fr);
-        D = *reinterpret_cast<const float *>(reinterpret_cast<const char *>(a.coef) +
-                                             ((unsigned)pz * pn + (unsigned)gy1[r] * a.nx + gx1[r]) * 4u);
+    auto load1 = [&](int r, int pz, R fr[Q], R &D) {
+        pull3<R, WALLS>(a.fin, a.stride, a.nx, a.ny, a.nz, gx1[r], gy1[r], pz, fr);
+        D = *reinterpret_cast<const R *>(reinterpret_cast<const char *>(a.coef) +
+                                         ((unsigned)pz * pn + (unsigned)gy1[r] * a.nx + gx1[r]) * (unsigned)sizeof(R));
     };
 
-    float fr[R1][Q];
-    float Dn[R1];
-    if (PF && have1(z0 - 1)) {
+    R fr[R1][Q];
+    R Dn[R1];
+    if (have1(z0 - 1)) {
 #pragma unroll
         for (int r = 0; r < R1; ++r)
             if (e1[r] < NE) load1(r, plane_of(z0 - 1), fr[r], Dn[r]);
@@ -336,24 +333,23 @@ __global__ __launch_bounds__(k2T) void k3_step2(Args3<float> a, int zc)
 #pragma unroll
             for (int r = 0; r < R1; ++r) {
                 if (e1[r] < NE) {
-                    if (!PF) load1(r, plane_of(p), fr[r], Dn[r]);
                     double f[Q];
 #pragma unroll
                     for (int q = 0; q < Q; ++q) f[q] = (double)fr[r][q];
                     collide3(a, f, (double)Dn[r]);
                     const int e = e1[r];
 #pragma unroll
-                    for (int i = 0; i < 9; ++i) sin_[s2][i][e] = (float)f[kIn[i]];
+                    for (int i = 0; i < 9; ++i) sin_[s2][i][e] = (R)f[kIn[i]];
 #pragma unroll
-                    for (int i = 0; i < 5; ++i) sup[s3][i][e] = (float)f[kUp[i]];
+                    for (int i = 0; i < 5; ++i) sup[s3][i][e] = (R)f[kUp[i]];
 #pragma unroll
-                    for (int i = 0; i < 5; ++i) sdn[s2][i][e] = (float)f[kDn[i]];
+                    for (int i = 0; i < 5; ++i) sdn[s2][i][e] = (R)f[kDn[i]];
                 }
             }
         }
         lds_barrier();
         // ---- loads for the next plane's step 1, in flight during step 2
-        if (PF && p + 1 <= zend && have1(p + 1)) {
+        if (p + 1 <= zend && have1(p + 1)) {
 #pragma unroll
             for (int r = 0; r < R1; ++r)
                 if (e1[r] < NE) load1(r, plane_of(p + 1), fr[r], Dn[r]);
@@ -367,7 +363,7 @@ __global__ __launch_bounds__(k2T) void k3_step2(Args3<float> a, int zc)
             const int dp = rr & 1;             // plane qz + 1: -z slot
             const bool blo = WALLS && qz == 0, bhi = WALLS && qz == a.nz - 1;
             const int e = e2;
-            float g[Q];
+            R g[Q];
             g[0] = sin_[i0][0][e];
             g[1] = sin_[i0][1][e - 1];
             g[2] = sin_[i0][2][e + 1];
@@ -407,12 +403,12 @@ __global__ __launch_bounds__(k2T) void k3_step2(Args3<float> a, int zc)
             double f[Q];
 #pragma unroll
             for (int q = 0; q < Q; ++q) f[q] = (double)g[q];
-            collide3(a, f, (double)*reinterpret_cast<const float *>(
-                               reinterpret_cast<const char *>(a.coef) + c * 4u));
+            collide3(a, f, (double)*reinterpret_cast<const R *>(
+                               reinterpret_cast<const char *>(a.coef) + c * (unsigned)sizeof(R)));
 #pragma unroll
             for (int q = 0; q < Q; ++q)
-                *reinterpret_cast<float *>(reinterpret_cast<char *>(a.fout + (size_t)q * a.stride) + c * 4u) =
-                    (float)f[q];
+                *reinterpret_cast<R *>(reinterpret_cast<char *>(a.fout + (size_t)q * a.stride) +
+                                       c * (unsigned)sizeof(R)) = (R)f[q];
         }
         // the next step 1 overwrites the slots of planes p - 1 (two-slot
         // rings) and p - 2 (+z ring)
@@ -630,6 +626,7 @@ struct lbm3d_handle {
     double prev_u[3];
     bool have_prev;
     double *host_res;
+    int shape;          // tile of the two-step kernel, or single steps (plan_steps)
     int zchunk;         // planes per workgroup run of the two-step kernel
 };
 
@@ -671,43 +668,98 @@ void launch_fields(const lbm3d_handle *h, double *u, double *rho, double *part)
                        u, rho, part);
 }
 
-// Planes per workgroup run: the number of runs per column that minimises
-// (waves of workgroups over the CUs, one resident per CU) x (planes per run
-// + the two extra step-1 planes), so the grid neither leaves CUs idle in its
-// last wave nor repeats many halo planes.
-int zchunk_for(int nx, int ny, int nz)
+// How a solver steps: two steps per launch on one of the tiles below with runs
+// of zc planes, or single steps, whichever is predicted to take less time:
+//   two steps: 3.5 us + rounds of resident workgroups x (zc + 2) planes x
+//     max(a plane's chain of barriers and reads, the bytes that the resident
+//     workgroups move per plane / the rate), 6.6 TB/s while both buffers fit the
+//     256 MB last-level cache, 4.5 TB/s beyond;
+//   a single step: 2.2 us + its bytes at 5.2 to 8.5 TB/s, more where rows leave
+//     lanes idle.
+// Measured (us per step; before, FP32 state always took two steps on 64 x 8 tiles
+// and FP64 state single steps): FP32 24^3 14.5 -> 3.2 and 64^3 14.3 -> 7.5 (single
+// steps), 30 x 200 x 40 15.3 -> 8.3 (16 x 8), 128^3 42.5 and 256^3 306 as before
+// (64 x 8); FP64 64^3 12.6 -> 10.3 and 111 x 90 x 75 35.6 -> 25.3 (16 x 8), 128^3
+// 123.9 -> 76.1 and 256^3 1029 -> 628 (64 x 4). Narrow tiles read partial lines,
+// which costs most from HBM. Every choice gives the same state bit for bit.
+struct TileInfo {
+    int ix, iy, resident;       // resident workgroups per CU
+    double chain[2], extra[2];  // us of one plane at least, and bytes moved over the tile's own: in cache, from HBM
+};
+enum { kSingle = -1, kWide8, kWide4, kNarrow, kTiles };
+constexpr TileInfo kTile32[kTiles] = {{64, 8, 1, {2.75, 4.4}, {1.0, 1.0}},
+                                      {0, 0, 0, {}, {}},
+                                      {16, 8, 4, {1.6, 2.2}, {1.35, 1.5}}};
+constexpr TileInfo kTile64[kTiles] = {{0, 0, 0, {}, {}},
+                                      {64, 4, 1, {3.0, 4.4}, {1.0, 1.0}},
+                                      {16, 8, 2, {2.4, 3.6}, {1.05, 1.15}}};
+
+void plan_steps(const lbm3d_params &p, int *shape, int *zchunk)
 {
-    const int64_t cols = (int64_t)((nx + k2IX - 1) / k2IX) * ((ny + k2IY - 1) / k2IY);
-    const int64_t slots = std::max(1, lbm::device_cu_count());
-    int best_zc = nz;
-    int64_t best = -1;
-    for (int runs = 1; runs <= nz; ++runs) {
-        const int zc = (nz + runs - 1) / runs;
-        if (runs > 1 && (nz + zc - 1) / zc != runs) continue;  // same zc as a smaller count
-        const int64_t waves = (cols * runs + slots - 1) / slots;
-        const int64_t cost = waves * (zc + 2);
-        if (best < 0 || cost < best) {
-            best = cost;
-            best_zc = zc;
+    const bool f64 = p.pop_dtype == LBM_F64;
+    const double el = f64 ? 8.0 : 4.0;
+    const double cells = (double)p.nx * p.ny * p.nz, bytes = 39.0 * el * cells;
+    const bool cached = bytes < 240e6;
+    const double lanes = (double)p.nx / (kTX * ((p.nx + kTX - 1) / kTX));
+    const double one = bytes < 64e6 ? 8.5e6 : bytes < 150e6 ? 7.5e6 : cached ? 7.0e6 : 5.2e6;  // bytes per us
+    double best = 2.0 * (2.2 + bytes / one * (1.0 + 0.7 * (1.0 - lanes)));
+    *shape = kSingle;
+    *zchunk = 1;
+    const int64_t cus = std::max(1, lbm::device_cu_count());
+    for (int t = 0; t < kTiles; ++t) {
+        const TileInfo &ti = f64 ? kTile64[t] : kTile32[t];
+        if (!ti.ix) continue;
+        const int64_t cols = (int64_t)((p.nx + ti.ix - 1) / ti.ix) * ((p.ny + ti.iy - 1) / ti.iy);
+        const int64_t slots = cus * ti.resident;
+        for (int runs = 1; runs <= p.nz; ++runs) {
+            const int zc = (p.nz + runs - 1) / runs;
+            if (zc < 2) break;
+            if (runs > 1 && (p.nz + zc - 1) / zc != runs) continue;  // same zc as a smaller count
+            const int64_t wgs = cols * runs;
+            const double rounds = (double)((wgs + slots - 1) / slots);
+            const double moved = (double)std::min(wgs, slots) * p.nx * p.ny / (double)cols * 39.0 * el * ti.extra[!cached];
+            // (small workgroups that share a CU also lengthen each other's chains)
+            const double share = ti.resident == 4 ? 0.4 * std::ceil((double)std::min(wgs, slots) / (double)cus) : 0.0;
+            const double plane = std::max(ti.chain[!cached] + share, moved / (cached ? 6.6e6 : 4.5e6));
+            const double us = 3.5 + rounds * (zc + 2) * plane;
+            if (us < best) {
+                best = us;
+                *shape = t;
+                *zchunk = zc;
+            }
         }
-        if (zc <= 8) break;
     }
-    return best_zc;
 }
 
-template <bool W>
-void launch_step2(const lbm3d_handle *h)
+template <typename R, bool W, int IX, int IY, int T>
+void launch_tile(const lbm3d_handle *h)
 {
     const int zc = h->zchunk;
-    const int nt = ((h->p.nx + k2IX - 1) / k2IX) * ((h->p.ny + k2IY - 1) / k2IY) *
-                   ((h->p.nz + zc - 1) / zc);
-    hipLaunchKernelGGL((k3_step2<W>), dim3(nt), dim3(k2T), 0, h->stream, args_of<float>(h), zc);
+    const int nt = ((h->p.nx + IX - 1) / IX) * ((h->p.ny + IY - 1) / IY) * ((h->p.nz + zc - 1) / zc);
+    hipLaunchKernelGGL((k3_step2<R, W, IX, IY, T>), dim3(nt), dim3(T), 0, h->stream, args_of<R>(h), zc);
 }
 
-// Two steps in one launch (FP32 state only).
+template <typename R, bool W>
+void launch_step2(const lbm3d_handle *h)
+{
+    if constexpr (sizeof(R) == 4) {
+        if (h->shape == kWide8) return launch_tile<R, W, 64, 8, 512>(h);
+    }
+    if constexpr (sizeof(R) == 8) {
+        if (h->shape == kWide4) return launch_tile<R, W, 64, 4, 448>(h);
+    }
+    launch_tile<R, W, 16, 8, 192>(h);
+}
+
+// Two steps in one launch.
 void step_twice(const lbm3d_handle *h)
 {
-    if (h->p.walls_z != 0) launch_step2<true>(h); else launch_step2<false>(h);
+    const bool w = h->p.walls_z != 0;
+    if (h->p.pop_dtype == LBM_F64) {
+        if (w) launch_step2<double, true>(h); else launch_step2<double, false>(h);
+    } else {
+        if (w) launch_step2<float, true>(h); else launch_step2<float, false>(h);
+    }
 }
 
 void step_once(const lbm3d_handle *h)
@@ -776,7 +828,7 @@ extern "C" lbm_status lbm3d_init(lbm3d_handle **out, const lbm3d_params *p, cons
     h->L = L;
     h->stream = stream;
     h->ws = static_cast<char *>(d_ws);
-    h->zchunk = zchunk_for(p->nx, p->ny, p->nz);
+    plan_steps(*p, &h->shape, &h->zchunk);
     if (hipHostMalloc((void **)&h->host_res, 4 * sizeof(double), hipHostMallocDefault) != hipSuccess) {
         delete h;
         return set_error(LBM_EDEVICE, "lbm3d_init: hipHostMalloc failed");
@@ -823,8 +875,7 @@ extern "C" lbm_status lbm3d_step(lbm3d_handle *h, int64_t max_steps, double tol,
     while (done < max_steps) {
         // two steps per launch unless a check or the end falls in between
         const int64_t to_check = check_every > 0 ? check_every - done % check_every : max_steps - done;
-        const int n = (h->p.pop_dtype == LBM_F32_SHIFTED &&
-                       std::min<int64_t>(to_check, max_steps - done) >= 2) ? 2 : 1;
+        const int n = (h->shape != kSingle && std::min<int64_t>(to_check, max_steps - done) >= 2) ? 2 : 1;
         if (n == 2)
             step_twice(h);
         else
