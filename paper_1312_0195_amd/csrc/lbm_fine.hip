@@ -33,6 +33,7 @@
 // types; FP32 storage only rounds the nine values written per cell.
 #include <hip/hip_runtime.h>
 
+#include <chrono>
 #include <cmath>
 #include <cstring>
 #include <algorithm>
@@ -884,9 +885,13 @@ __global__ __launch_bounds__(kBlock) void k_fields(StepArgs<R> a, double *__rest
     }
 }
 
-// Fixed-order sum of n (x, y) pairs into out[0..1], divided by ncells.
+// Fixed-order sum of n (x, y) pairs, divided by the number of cells, into
+// pinned host memory: out[0..1], then the number of the call in out[2], which
+// the host may wait for. (Adding up in the last workgroup of k_fields instead
+// was no faster at 64 x 64 cells and slower beyond, by 20 us at 256 x 1024 and
+// 500 us at 2048 x 2048: its counter takes 30 ns per workgroup.)
 __global__ __launch_bounds__(kBlock) void k_reduce_pairs(const double *__restrict__ partials,
-                                                         int n, double inv_cells,
+                                                         int n, double inv_cells, unsigned long long call,
                                                          double *__restrict__ out)
 {
     __shared__ double red[2][kBlock / 64];
@@ -925,6 +930,8 @@ __global__ __launch_bounds__(kBlock) void k_reduce_pairs(const double *__restric
         }
         out[0] = tx * inv_cells;
         out[1] = ty * inv_cells;
+        __hip_atomic_store(reinterpret_cast<unsigned long long *>(out) + 2, call, __ATOMIC_RELEASE,
+                           __HIP_MEMORY_SCOPE_SYSTEM);
     }
 }
 
@@ -1069,9 +1076,9 @@ __global__ __launch_bounds__(kBlock) void k_field_check(StepArgs<R> a, long long
     status[1] = flag;
     status[2] = flag >= 0;
     status[3] = 0;
-    host[0] = steps;
     host[1] = flag;
     host[2] = flag >= 0;
+    __hip_atomic_store(&host[0], steps, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // Full pre-collision populations of the current state, FP64 [9][ny][nx].
@@ -1129,7 +1136,7 @@ struct Layout {
     size_t elem;      // bytes per population element
     size_t stride;    // elements per population plane
     size_t cstride;   // elements per coefficient plane
-    size_t off_a, off_b, off_coef, off_force, off_part, off_res, off_flag, total;
+    size_t off_a, off_b, off_coef, off_force, off_part, off_flag, total;
     int nbx, nby;     // launch grid of the per-cell kernels
 };
 
@@ -1176,7 +1183,7 @@ Layout layout_of(const lbm_params *p)
     L.nbx = (p->nx + kBlock - 1) / kBlock;
     L.nby = p->ny;
     L.off_part = off; off = align_up(off + 2 * sizeof(double) * (size_t)L.nbx * L.nby);
-    L.off_res = off;  off = align_up(off + 4 * sizeof(double));
+    off = align_up(off + 4 * sizeof(double));  // free; the size that callers know stays
     L.off_flag = off; off = align_up(off + sizeof(int));
     L.total = off;
     return L;
@@ -1220,7 +1227,8 @@ struct lbm_handle {
     int64_t steps_total;
     double prev_u[2];
     bool have_prev;
-    double *host_res;   // pinned host copy of the reduction result
+    double *host_res;   // pinned: mean velocity, number of its call
+    unsigned long long means;  // mean velocities asked for
 };
 
 namespace lbm {
@@ -1449,20 +1457,47 @@ struct FieldsFn {
     }
 };
 
-lbm_status mean_velocity(lbm_handle *h, double out[2])
+// The mean velocity of the current state: queued here, fetched by wait_mean.
+void queue_mean(lbm_handle *h)
 {
     double *part = reinterpret_cast<double *>(h->ws + h->L.off_part);
-    double *res = reinterpret_cast<double *>(h->ws + h->L.off_res);
     dispatch<FieldsFn>(h, (double *)nullptr, (double *)nullptr, part);
-    const int nparts = h->L.nbx * h->L.nby;
-    hipLaunchKernelGGL(k_reduce_pairs, dim3(1), dim3(kBlock), 0, h->stream, part, nparts,
-                       1.0 / ((double)h->p.nx * h->p.ny), res);
+    hipLaunchKernelGGL(k_reduce_pairs, dim3(1), dim3(kBlock), 0, h->stream, part, h->L.nbx * h->L.nby,
+                       1.0 / ((double)h->p.nx * h->p.ny), ++h->means, h->host_res);
+}
+
+// Wait until a kernel has stored `value` to pinned memory, with more work
+// queued behind that kernel, so that waiting for the stream would idle the
+// device: the host looks for the value itself for up to 5 ms, beside which the
+// 10 us that an idle device loses are little, then waits for the stream.
+// 64 x 64 cells, a check every 100 steps: 80 us per interval, 90 with a copy
+// and a synchronisation.
+hipError_t wait_value(const void *at, unsigned long long value, hipStream_t stream)
+{
+    const auto *p = static_cast<const unsigned long long *>(at);
+    const auto end = std::chrono::steady_clock::now() + std::chrono::milliseconds(5);
+    while (std::chrono::steady_clock::now() < end) {
+        if (__atomic_load_n(p, __ATOMIC_ACQUIRE) == value) return hipSuccess;
+        __builtin_ia32_pause();
+    }
+    return hipStreamSynchronize(stream);
+}
+
+// more: work is queued behind it. With none the stream is waited for, which a
+// caller's own synchronisation (20 us after the bare result) then finds done.
+lbm_status wait_mean(lbm_handle *h, bool more, double out[2])
+{
     LBM_HIP(hipGetLastError());
-    LBM_HIP(hipMemcpyAsync(h->host_res, res, 2 * sizeof(double), hipMemcpyDeviceToHost, h->stream));
-    LBM_HIP(hipStreamSynchronize(h->stream));
+    LBM_HIP(more ? wait_value(h->host_res + 2, h->means, h->stream) : hipStreamSynchronize(h->stream));
     out[0] = h->host_res[0];
     out[1] = h->host_res[1];
     return LBM_OK;
+}
+
+lbm_status mean_velocity(lbm_handle *h, double out[2])
+{
+    queue_mean(h);
+    return wait_mean(h, false, out);
 }
 
 // Queue the steps of one stretch until at least `least` of them are queued.
@@ -1514,41 +1549,35 @@ lbm_status run_to_steady_field(const FieldRun &f, long long result[2])
     h.plan = plan_launches(h.p, true);
     const bool f64 = h.p.pop_dtype == LBM_F64;
     long long *host = nullptr;
-    hipEvent_t ev = nullptr;
     LBM_HIP(hipHostMalloc((void **)&host, 4 * sizeof(long long), hipHostMallocDefault));
     host[0] = host[1] = host[2] = 0;
-    hipError_t e = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
-    if (e == hipSuccess) {
-        const int n = h.p.nx * h.p.ny, nb = (n + kBlock - 1) / kBlock;
-        hipLaunchKernelGGL(k_zero_i32, dim3(1), dim3(64), 0, f.stream, reinterpret_cast<int *>(f.status), 8);
+    hipError_t e = hipSuccess;
+    const int n = h.p.nx * h.p.ny, nb = (n + kBlock - 1) / kBlock;
+    hipLaunchKernelGGL(k_zero_i32, dim3(1), dim3(64), 0, f.stream, reinterpret_cast<int *>(f.status), 8);
+    if (f64)
+        hipLaunchKernelGGL(k_rest<double>, dim3(nb), dim3(kBlock), 0, f.stream,
+                           reinterpret_cast<double *>(h.ws + h.L.off_a), (int)h.L.stride, n);
+    else
+        hipLaunchKernelGGL(k_rest<float>, dim3(nb), dim3(kBlock), 0, f.stream,
+                           reinterpret_cast<float *>(h.ws + h.L.off_a), (int)h.L.stride, n);
+    int64_t steps = 0, ahead = 0;  // ahead: steps of the current interval already queued
+    while (e == hipSuccess) {
+        queue_steps(&h, f.check_every - ahead, f.check_every);
+        steps += f.check_every;
         if (f64)
-            hipLaunchKernelGGL(k_rest<double>, dim3(nb), dim3(kBlock), 0, f.stream,
-                               reinterpret_cast<double *>(h.ws + h.L.off_a), (int)h.L.stride, n);
+            field_check<double>(h, f, steps, steps == f.check_every, host);
         else
-            hipLaunchKernelGGL(k_rest<float>, dim3(nb), dim3(kBlock), 0, f.stream,
-                               reinterpret_cast<float *>(h.ws + h.L.off_a), (int)h.L.stride, n);
-        int64_t steps = 0, ahead = 0;  // ahead: steps of the current interval already queued
-        while (e == hipSuccess) {
-            queue_steps(&h, f.check_every - ahead, f.check_every);
-            steps += f.check_every;
-            if (f64)
-                field_check<double>(h, f, steps, steps == f.check_every, host);
-            else
-                field_check<float>(h, f, steps, steps == f.check_every, host);
-            e = hipGetLastError();
-            if (e == hipSuccess) e = hipEventRecord(ev, f.stream);
-            ahead = steps < f.max_steps ? queue_steps(&h, f.check_every, kAhead) : 0;
-            if (e == hipSuccess) e = hipGetLastError();
-            if (e == hipSuccess) e = hipEventSynchronize(ev);
-            if (e != hipSuccess || host[2] != 0) break;
-        }
+            field_check<float>(h, f, steps, steps == f.check_every, host);
+        ahead = steps < f.max_steps ? queue_steps(&h, f.check_every, kAhead) : 0;
+        e = hipGetLastError();
+        if (e == hipSuccess) e = wait_value(host, (unsigned long long)steps, f.stream);
+        if (e != hipSuccess || host[2] != 0) break;
     }
     // what was queued ahead uses the workspace and the host's mirror
     const hipError_t es = hipStreamSynchronize(f.stream);
     if (e == hipSuccess) e = es;
     result[0] = host[0];
     result[1] = host[1];
-    if (ev) (void)hipEventDestroy(ev);
     (void)hipHostFree(host);
     return e == hipSuccess ? LBM_OK : hip_check(e, "lbm_coarse_solve");
 }
@@ -1596,6 +1625,7 @@ extern "C" lbm_status lbm_init(lbm_handle **out, const lbm_params *p, const doub
     const int n = p->nx * p->ny;
     const int nb = (n + kBlock - 1) / kBlock;
     hipLaunchKernelGGL(k_zero_i32, dim3(1), dim3(64), 0, stream, flag, 1);
+    reinterpret_cast<unsigned long long *>(h->host_res)[2] = 0;
     hipError_t e = hipGetLastError();
     if (e == hipSuccess) {
         if (p->pop_dtype == LBM_F64) {
@@ -1659,21 +1689,33 @@ extern "C" lbm_status lbm_step(lbm_handle *h, int64_t max_steps, double tol, int
     int64_t done = 0;
     bool last_checked = false;
     double u[2] = {0.0, 0.0};
-    while (done < max_steps) {
-        // several steps per launch unless a check or the end falls in between
+    // Several steps per launch unless a check or the end falls in between. The
+    // first launch after a check is queued before the host waits for the
+    // check's result: it writes the buffer that the state is not in, so it
+    // counts only once the run is known to go on.
+    auto depth = [&] {
         const int64_t to_check = check_every > 0 ? check_every - done % check_every : max_steps - done;
-        const int n = launch_depth(h, std::min<int64_t>(to_check, max_steps - done));
+        return launch_depth(h, std::min<int64_t>(to_check, max_steps - done));
+    };
+    auto launch = [&](int n) {
         if (n >= 2)
             dispatch<StepDFn>(h, n);
         else
             dispatch<StepFn>(h);
+        return n;
+    };
+    int ahead = 0;  // steps of a launch that is queued and not counted yet
+    while (done < max_steps) {
+        const int n = ahead ? ahead : launch(depth());
+        ahead = 0;
         h->cur ^= 1;
         done += n;
         h->steps_total += n;
         last_checked = false;
         if (check_every > 0 && done % check_every == 0) {
-            LBM_HIP(hipGetLastError());
-            lbm_status s = mean_velocity(h, u);
+            queue_mean(h);
+            if (done < max_steps) ahead = launch(depth());
+            lbm_status s = wait_mean(h, ahead > 0, u);
             if (s != LBM_OK) return s;
             last_checked = true;
             if (!std::isfinite(u[0]) || !std::isfinite(u[1])) {
@@ -1695,6 +1737,7 @@ extern "C" lbm_status lbm_step(lbm_handle *h, int64_t max_steps, double tol, int
         }
     }
     LBM_HIP(hipGetLastError());
+    if (ahead) LBM_HIP(hipStreamSynchronize(h->stream));  // not needed, but it uses the workspace
     if (steps_done) *steps_done = done;
     if (mean_u) {
         if (!last_checked) {
