@@ -1001,10 +1001,12 @@ static_assert(kLine1 * kSide * 4 <= kActElems * 2, "the conv1 partial sums reuse
 // is one patch's chain of phases: 6900 MFMAs (11.5 us at the full rate), the
 // 200 KB of stored activations and the barriers between the layers. The next
 // plane's activations and the dX weights are read into registers while the
-// dW products of the layer before run. Measured at batch 256: 63 us, against
+// dW products of the layer before run. Measured at batch 256: 52 us, against
 // 227 us with operands gathered element by element and the bias and conv1
 // sums on 32 and 288 threads, pixel by pixel; the whole training step with
-// the head's backward, the reduction and Adam 95 us against 380.
+// the head's backward, the reduction and Adam 86 us against 380. What is left:
+// dW 3.5 us per layer (1 MB of transposing reads from LDS), dX 2.2, the reads
+// of a3 and the start 8, conv1 3.
 __global__ __launch_bounds__(kT) void k_backward(BwdArgs a)
 {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -1035,21 +1037,37 @@ __global__ __launch_bounds__(kT) void k_backward(BwdArgs a)
     float g1 = 0.0f;                        // entry tid of (W1, b1)
     float ghd[3] = {0.0f, 0.0f, 0.0f};      // entries tid, tid + 512, tid + 1024 of the head's gradient
     float loss = 0.0f;                      // thread 0
-    for (int i = tid; i < kNHead; i += kT) hp[i] = a.prm[oM1 + i];
+    {
+        float v[3];  // read together
+#pragma unroll
+        for (int r = 0; r < 3; ++r) v[r] = a.prm[oM1 + min(tid + r * kT, kNHead - 1)];
+#pragma unroll
+        for (int r = 0; r < 3; ++r)
+            if (tid + r * kT < kNHead) hp[tid + r * kT] = v[r];
+    }
     const size_t plane = (size_t)a.batch * kPix * kC;
     for (int b = blockIdx.x; b < a.batch; b += gridDim.x) {
-        asm volatile("" : "+v"(tid));  // what follows from it is not kept over the whole loop
+        // An address that follows from tid is computed again after each of
+        // these lines instead of being kept over the phases between its uses:
+        // kept, they spilled 140 B, the prefetched planes among it, so every
+        // prefetch was waited for at once (batch 256: 62 us, with the next 52).
+        asm volatile("" : "+v"(tid));
         const int lane = tid & 63;
         const __bf16 *act = a.acts + (size_t)b * kPix * kC;
+        // the symmetry and the head's input first: reads return in order, and
+        // the head then runs while a3 is on its way (without sym any byte is read)
+        int sym = *(a.sym ? a.sym + b : reinterpret_cast<const int8_t *>(a.target));
+        float zv = a.pool[(size_t)b * kZ + min(tid, kZ - 1)];
         bf16x8 nx[kActVecs];
         fetch_act(nx, tid, act + 2 * plane);  // a3, the input of conv4
         unsigned mk[kActVecs];
 #pragma unroll
         for (int i = 0; i < kActVecs; ++i) mk[i] = a.mask4[(size_t)b * kPix + ((tid + i * kT) >> 2)];
-        const int sym = a.sym ? (int)a.sym[b] : 0;
+        asm volatile("" : "+v"(sym), "+v"(zv));  // all reads above are under way
+        sym = a.sym ? sym : 0;
         const float *lk = a.logk + (size_t)b * kPix;
         const float v0 = lk[sym_src(tid, sym)], v1 = lk[sym_src(tid + kT, sym)];
-        if (tid < kZ) z[tid] = a.pool[(size_t)b * kZ + tid];
+        if (tid < kZ) z[tid] = zv;
         __syncthreads();
         // ---- head, FP32: loss = mean over the batch and both outputs of
         // (prediction - target)^2
@@ -1086,12 +1104,14 @@ __global__ __launch_bounds__(kT) void k_backward(BwdArgs a)
             }
         }
         put_act(buf1, tid, nx);
+        asm volatile("" : "+v"(tid));
         fetch_act(nx, tid, act + plane);  // a2
         xs[tid] = v0 - m;
         xs[tid + kT] = v1 - m;
         if (tid < kSide) xs[kPix + tid] = v0 - m;              // row 32 = row 0
         if (tid >= kT - kSide) xs[tid + kT - kPix] = v1 - m;  // row -1 = row 31
         __syncthreads();
+        asm volatile("" : "+v"(tid));
 #pragma unroll
         for (int r = 0; r < 3; ++r) {
             const int i = tid + r * kT;  // head parameter oM1 + i
@@ -1112,17 +1132,24 @@ __global__ __launch_bounds__(kT) void k_backward(BwdArgs a)
             dpool[tid] = s;
         }
         __syncthreads();
+        asm volatile("" : "+v"(tid));
         // ---- dZ4 = dpool / 1024 where a4 > 0
+        // (the rounded values taken once: selected before rounding, each of the
+        // 64 was a branch around an LDS read: 4.3 us, 1.5 now)
+        const int c = tid & 3;  // of every chunk of this thread
+        __bf16 dp[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) dp[j] = (__bf16)(dpool[c * 8 + j] * (1.0f / kPix));
 #pragma unroll
         for (int i = 0; i < kActVecs; ++i) {
-            const int chunk = tid + i * kT, c = chunk & 3;
+            const int chunk = tid + i * kT;
             // channel 16 ct + 4 k + j is bit 4 ct + j of the pixel's byte k
             const unsigned bits = (mk[i] >> (16 * (c & 1))) >> (4 * (c >> 1));
             bf16x8 v;
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
                 const bool on = (bits >> ((j & 3) + 8 * (j >> 2))) & 1;
-                v[j] = (__bf16)(on ? dpool[c * 8 + j] * (1.0f / kPix) : 0.0f);
+                v[j] = on ? dp[j] : (__bf16)0.0f;
             }
             put_chunk(buf0, chunk, v);
         }
@@ -1130,6 +1157,7 @@ __global__ __launch_bounds__(kT) void k_backward(BwdArgs a)
         lds_bf16 *dZ = buf0, *X = buf1;
 #pragma unroll
         for (int l = 3; l >= 1; --l) {  // layer l + 1 of the network: conv2..4 are l = 1..3
+            asm volatile("" : "+v"(tid));
             typedef __attribute__((address_space(1))) const bf16x8 glb_bf16x8;
             const __bf16 *wbl = a.wb + (size_t)(l - 1) * 9 * kC * kC;
             asm volatile("" : "+s"(wbl));  // keeps the loads here: hoisted, three layers' weights spill
@@ -1167,6 +1195,7 @@ __global__ __launch_bounds__(kT) void k_backward(BwdArgs a)
             dZ = X;
             X = t;
             if (l > 1) {
+                asm volatile("" : "+v"(tid));
                 put_act(X, tid, nx);
                 if (l == 3) fetch_act(nx, tid, act);  // a1
                 __syncthreads();
@@ -1175,6 +1204,7 @@ __global__ __launch_bounds__(kT) void k_backward(BwdArgs a)
         // ---- layer 1 (1 -> 32), FP32: each thread two channels of one row,
         // with the 3 x 3 window of the input in registers
         {
+            asm volatile("" : "+v"(tid));
             const int cp = tid & 15, y = tid >> 4;
             float s[9][2], sb[2] = {0.0f, 0.0f};
 #pragma unroll
