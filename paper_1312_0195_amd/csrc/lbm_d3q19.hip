@@ -677,9 +677,9 @@ void launch_fields(const lbm3d_handle *h, double *u, double *rho, double *part)
 //   a single step: 2.2 us + its bytes at 5.2 to 8.5 TB/s, more where rows leave
 //     lanes idle.
 // Measured (us per step; before, FP32 state always took two steps on 64 x 8 tiles
-// and FP64 state single steps): FP32 24^3 14.5 -> 3.2 and 64^3 14.3 -> 7.5 (single
-// steps), 30 x 200 x 40 15.3 -> 8.3 (16 x 8), 128^3 42.5 and 256^3 306 as before
-// (64 x 8); FP64 64^3 12.6 -> 10.3 and 111 x 90 x 75 35.6 -> 25.3 (16 x 8), 128^3
+// and FP64 state single steps): FP32 24^3 14.5 -> 3.2 (single steps),
+// 64^3 14.3 -> 7.5 (64 x 8, runs of 2 planes), 30 x 200 x 40 15.3 -> 8.3 (16 x 8),
+// 128^3 42.5 and 256^3 306 as before (64 x 8); FP64 64^3 12.6 -> 10.3 and 111 x 90 x 75 35.6 -> 25.3 (16 x 8), 128^3
 // 123.9 -> 76.1 and 256^3 1029 -> 628 (64 x 4). Narrow tiles read partial lines,
 // which costs most from HBM. Every choice gives the same state bit for bit.
 struct TileInfo {
@@ -694,7 +694,7 @@ constexpr TileInfo kTile64[kTiles] = {{0, 0, 0, {}, {}},
                                       {64, 4, 1, {3.0, 4.4}, {1.0, 1.0}},
                                       {16, 8, 2, {2.4, 3.6}, {1.05, 1.15}}};
 
-void plan_steps(const lbm3d_params &p, int *shape, int *zchunk)
+void plan_steps(const lbm3d_params &p, int64_t cus, int *shape, int *zchunk)
 {
     const bool f64 = p.pop_dtype == LBM_F64;
     const double el = f64 ? 8.0 : 4.0;
@@ -705,16 +705,16 @@ void plan_steps(const lbm3d_params &p, int *shape, int *zchunk)
     double best = 2.0 * (2.2 + bytes / one * (1.0 + 0.7 * (1.0 - lanes)));
     *shape = kSingle;
     *zchunk = 1;
-    const int64_t cus = std::max(1, lbm::device_cu_count());
     for (int t = 0; t < kTiles; ++t) {
         const TileInfo &ti = f64 ? kTile64[t] : kTile32[t];
         if (!ti.ix) continue;
         const int64_t cols = (int64_t)((p.nx + ti.ix - 1) / ti.ix) * ((p.ny + ti.iy - 1) / ti.iy);
         const int64_t slots = cus * ti.resident;
-        for (int runs = 1; runs <= p.nz; ++runs) {
-            const int zc = (p.nz + runs - 1) / runs;
-            if (zc < 2) break;
-            if (runs > 1 && (p.nz + zc - 1) / zc != runs) continue;  // same zc as a smaller count
+        // every number of runs once, each with its shortest: about 2 sqrt(nz) of them (trying each
+        // number up to nz took 9 ms for a column of a million planes)
+        for (int zc = p.nz; zc >= 2; --zc) {
+            const int runs = (p.nz - 1) / zc + 1;
+            zc = (p.nz - 1) / runs + 1;
             const int64_t wgs = cols * runs;
             const double rounds = (double)((wgs + slots - 1) / slots);
             const double moved = (double)std::min(wgs, slots) * p.nx * p.ny / (double)cols * 39.0 * el * ti.extra[!cached];
@@ -808,6 +808,21 @@ extern "C" size_t lbm3d_workspace_bytes(const lbm3d_params *p)
     return layout_of(p).total;
 }
 
+extern "C" lbm_status lbm3d_plan_of(const lbm3d_params *p, int32_t cus, int32_t out[4])
+{
+    std::string why;
+    if (!out || cus < 1 || !params_ok(p, why)) return set_error(LBM_EINVAL, "lbm3d_plan_of: " + why);
+    int shape = 0, zc = 0;
+    plan_steps(*p, cus, &shape, &zc);
+    const TileInfo none{};
+    const TileInfo &ti = shape == kSingle ? none : p->pop_dtype == LBM_F64 ? kTile64[shape] : kTile32[shape];
+    out[0] = shape == kSingle ? 1 : 2;
+    out[1] = ti.ix;
+    out[2] = ti.iy;
+    out[3] = zc;
+    return LBM_OK;
+}
+
 extern "C" lbm_status lbm3d_init(lbm3d_handle **out, const lbm3d_params *p, const double *d_kappa,
                                  void *d_ws, size_t ws_bytes, hipStream_t stream)
 {
@@ -828,7 +843,7 @@ extern "C" lbm_status lbm3d_init(lbm3d_handle **out, const lbm3d_params *p, cons
     h->L = L;
     h->stream = stream;
     h->ws = static_cast<char *>(d_ws);
-    plan_steps(*p, &h->shape, &h->zchunk);
+    plan_steps(*p, std::max(1, lbm::device_cu_count()), &h->shape, &h->zchunk);
     if (hipHostMalloc((void **)&h->host_res, 4 * sizeof(double), hipHostMallocDefault) != hipSuccess) {
         delete h;
         return set_error(LBM_EDEVICE, "lbm3d_init: hipHostMalloc failed");

@@ -80,3 +80,8 @@ void fine_coef_planes(const lbm_params &p, char *ws, char **coef, char **force);
 lbm_status run_to_steady_field(const FieldRun &f, long long result[2]);
 
 }  // namespace lbm
+
+// What a D3Q19 solver of these parameters does on a device of `cus` compute
+// units: steps per launch, tile (x, y) and planes per run (0, 0, 1 for single
+// steps). Host only; for the tests, which have to reach every kernel.
+extern "C" lbm_status lbm3d_plan_of(const lbm3d_params *p, int32_t cus, int32_t out[4]);
