@@ -1379,23 +1379,32 @@ struct StepDFn {
 // a launch's own 2.7 us, the state through HBM once at 8 TB/s, and per round of
 // resident tiles the D steps, each `wave` us per wavefront and SIMD in it (at
 // least the 0.42 us that one step's chain of LDS reads, collision, writes and
-// barrier takes). Fitted to launches of 64^2 to 2048^2 grids; within 10% of
-// them: 64^2 FP32 state D = 10 6.9 us (measured 7.0), 400^2 FP64 with a force
-// D = 8 14.3 (14.8), 700^2 FP32 D = 8 22.1 (22.4), 1000^2 FP32 arithmetic D = 7
-// 24.6 (24.4), 2048^2 FP64 D = 6 179 (184).
+// barrier takes). Fitted to launches of 64^2 to 2048^2 grids: 64^2 FP32 state
+// D = 10 6.9 us (measured 7.0), 400^2 FP64 with a force D = 8 14.3 (14.8), 700^2
+// FP32 D = 8 22.1 (22.4), 2048^2 FP64 D = 6 179 (184). Runs of 200 to 600 steps
+// took 0.95 to 1.3 times their prediction over all types, coefficients and
+// sizes (most where one or two rounds of tiles take the whole launch); a plan
+// needs the order of its choices, not the time.
+// FP32 state with a tensor in FP64 arithmetic holds 84 to 108 registers in
+// k_rows, so one workgroup of 12 waves per CU (lone), whose rounds do not
+// overlap. Planned as if two were resident, 600^2 took 3.35 us per step, 1000^2
+// 6.70 and 3000 x 2000 39.0; now 2.73, 6.17 and 37.4 (other sizes within 2% or
+// faster; over 18 grids the plan is 0.6% off the best tile and depth tried, on
+// average, and was 2.5%).
 double launch_us(const lbm_params &p, bool force, int cus, int shape, int D, int tx, int ty)
 {
     const bool f64 = p.pop_dtype == LBM_F64, fast = p.pop_dtype == LBM_F32_FAST;
     const double nt = (double)((p.nx + tx - 1) / tx) * ((p.ny + ty - 1) / ty);
     const int ax = tx + 2 * (D - 1), ay = ty + 2 * (D - 1);
-    const bool two = shape == kRows768 || shape == kRows1024 || shape == kTile32;
+    const bool lone = shape == kRows768 && !fast && p.perm_kind == LBM_PERM_TENSOR;
+    const bool two = (shape == kRows768 && !lone) || shape == kRows1024 || shape == kTile32;
     const double r = (two && nt > cus) ? 2.0 : 1.0;  // tiles of a CU at once
     // rounds of tiles; a last one that fills at most half of the places runs one tile per CU
     const double full = nt / (cus * r), frac = full - std::floor(full);
-    const double rounds = full > 4.0 ? full + 0.2
-                                     : std::floor(full) + (frac == 0.0 ? 0.0 : (r == 2.0 && frac <= 0.5) ? 0.6 : 1.0);
-    const double wave = fast ? 0.063 : p.scheme == LBM_SCHEME_GUO ? 0.185 : f64 ? 0.127 : 0.112;
-    double t = r == 1.0 && rounds > 1.0 ? 2.0 : 0.0;  // a lone tile waits for its own reads
+    const double rounds = full > (lone ? 8.0 : 4.0) ? full + 0.2
+                          : std::floor(full) + (frac == 0.0 ? 0.0 : (r == 2.0 && frac <= 0.5) ? 0.6 : 1.0);
+    const double wave = fast ? 0.063 : p.scheme == LBM_SCHEME_GUO ? 0.185 : f64 ? 0.127 : lone ? 0.118 : 0.112;
+    double t = r == 1.0 && rounds > 1.0 ? (lone ? 1.0 : 2.0) : 0.0;  // a lone tile waits for its own reads
     const double lat = r == 1.0 || full <= 1.0 ? 0.25 : 0.12;
     for (int s = 0; s < D; ++s) t += std::max(0.42, lat + wave * r * ax * (ay - 2 * s) / 256.0);
     const double planes = 19.0 + (force ? 2.0 : 0.0) + (p.perm_kind == LBM_PERM_TENSOR ? 3.0 : 0.0);
@@ -1411,11 +1420,10 @@ double launch_us(const lbm_params &p, bool force, int cus, int shape, int D, int
 // per step against 48 x 24 tiles on 6 CUs); large ones the 64-wide rows with FP32
 // state (2048^2: FP32 arithmetic 15.0 -> 13.1, FP64 arithmetic 19.3 -> 17.6) and
 // 32-wide tiles with FP64 state (38.7 -> 30.7).
-Plan plan_launches(const lbm_params &p, bool force)
+Plan plan_launches(const lbm_params &p, bool force, int cus)
 {
     Plan pl{};
     const bool f64 = p.pop_dtype == LBM_F64, fast = p.pop_dtype == LBM_F32_FAST;
-    const int cus = std::max(1, device_cu_count());
     for (int D = 2; D <= kMaxDepth; ++D) {
         Launch best{kTile1024, 1, 1, 1e30};
         auto offer = [&](int shape, int tx, int ty) {
@@ -1456,10 +1464,11 @@ Plan plan_launches(const lbm_params &p, bool force)
     return pl;
 }
 
-int launch_depth(const lbm_handle *h, int64_t room)
+int launch_depth(const Plan &pl, int64_t room)
 {
-    return room > kPlanRoom ? h->plan.longest : h->plan.first[std::max<int64_t>(room, 1)];
+    return room > kPlanRoom ? pl.longest : pl.first[std::max<int64_t>(room, 1)];
 }
+
 template <typename R, bool W, int PK, bool FF>
 struct FieldsFn {
     static void run(const lbm_handle *h, double *u, double *rho, double *part)
@@ -1516,7 +1525,7 @@ int64_t queue_steps(lbm_handle *h, int64_t stretch, int64_t least)
 {
     int64_t n = 0;
     while (n < std::min(stretch, least)) {
-        const int d = launch_depth(h, stretch - n);
+        const int d = launch_depth(h->plan, stretch - n);
         if (d >= 2)
             dispatch<StepDFn>(h, d);
         else
@@ -1557,7 +1566,7 @@ lbm_status run_to_steady_field(const FieldRun &f, long long result[2])
     h.stream = f.stream;
     h.ws = f.ws;
     h.has_force = true;
-    h.plan = plan_launches(h.p, true);
+    h.plan = plan_launches(h.p, true, std::max(1, device_cu_count()));
     const bool f64 = h.p.pop_dtype == LBM_F64;
     long long *host = nullptr;
     LBM_HIP(hipHostMalloc((void **)&host, 4 * sizeof(long long), hipHostMallocDefault));
@@ -1604,6 +1613,22 @@ extern "C" size_t lbm_workspace_bytes(const lbm_params *p)
     return layout_of(p).total;
 }
 
+extern "C" lbm_status lbm_plan_of(const lbm_params *p, int32_t force, int32_t cus, int64_t steps, int32_t out[4],
+                                  double *us)
+{
+    std::string why;
+    if (!out || !us || cus < 1 || steps < 1 || !params_ok(p, why))
+        return set_error(LBM_EINVAL, "lbm_plan_of: " + why);
+    const Plan pl = plan_launches(*p, force != 0, cus);
+    const int d = launch_depth(pl, steps);
+    out[0] = d;
+    out[1] = d == 1 ? -1 : pl.at[d].shape;
+    out[2] = d == 1 ? 0 : pl.at[d].tx;
+    out[3] = d == 1 ? 0 : pl.at[d].ty;
+    *us = pl.at[d].us;
+    return LBM_OK;
+}
+
 extern "C" lbm_status lbm_init(lbm_handle **out, const lbm_params *p, const double *d_perm,
                                const double *d_force, void *d_ws, size_t ws_bytes,
                                hipStream_t stream)
@@ -1627,7 +1652,7 @@ extern "C" lbm_status lbm_init(lbm_handle **out, const lbm_params *p, const doub
     h->ws = static_cast<char *>(d_ws);
     h->cur = 0;
     h->has_force = d_force != nullptr;
-    h->plan = plan_launches(*p, h->has_force);
+    h->plan = plan_launches(*p, h->has_force, std::max(1, device_cu_count()));
     if (hipHostMalloc((void **)&h->host_res, 4 * sizeof(double), hipHostMallocDefault) != hipSuccess) {
         delete h;
         return set_error(LBM_EDEVICE, "lbm_init: hipHostMalloc failed");
@@ -1706,7 +1731,7 @@ extern "C" lbm_status lbm_step(lbm_handle *h, int64_t max_steps, double tol, int
     // counts only once the run is known to go on.
     auto depth = [&] {
         const int64_t to_check = check_every > 0 ? check_every - done % check_every : max_steps - done;
-        return launch_depth(h, std::min<int64_t>(to_check, max_steps - done));
+        return launch_depth(h->plan, std::min<int64_t>(to_check, max_steps - done));
     };
     auto launch = [&](int n) {
         if (n >= 2)

@@ -81,6 +81,13 @@ lbm_status run_to_steady_field(const FieldRun &f, long long result[2]);
 
 }  // namespace lbm
 
+// The first launch of a fine-grid solver of these parameters over a stretch of
+// `steps` steps, on a device of `cus` compute units: steps, kernel (in the order
+// of lbm_fine.hip's Shape, -1: k_step) and tile, and its predicted time. Host
+// only; for the tests, which have to reach every kernel.
+extern "C" lbm_status lbm_plan_of(const lbm_params *p, int32_t force, int32_t cus, int64_t steps, int32_t out[4],
+                                  double *us);
+
 // What a D3Q19 solver of these parameters does on a device of `cus` compute
 // units: steps per launch, tile (x, y) and planes per run (0, 0, 1 for single
 // steps). Host only; for the tests, which have to reach every kernel.

@@ -2,6 +2,8 @@
 import ctypes
 import time
 
+import pytest
+
 from paper_1312_0195_amd import lbm as L
 
 
@@ -20,3 +22,29 @@ def test_a_column_of_many_planes_is_planned_at_once():
     t = time.perf_counter()
     assert _plan3(1, 1, (1 << 30) - 65537, L.LBM_F32_SHIFTED)[0] in (1, 2)
     assert time.perf_counter() - t < 0.2
+
+
+def _plan(nx, ny, dtype, steps, walls=0, force=0, perm=1, scheme=0, gy=3e-7):
+    """((steps, kernel, tile x, tile y), predicted us) of the first launch"""
+    out, us = (ctypes.c_int32 * 4)(), ctypes.c_double()
+    p = L.make_params(nx, ny, 0.8, 0.4, 0.1, 1.0, 1e-6, gy, walls, dtype, perm, scheme)
+    assert L.lib().lbm_plan_of(ctypes.byref(p), force, 256, ctypes.c_int64(steps), out, ctypes.byref(us)) == L.LBM_OK
+    return tuple(out), us.value
+
+
+def _run_us(n, steps, **kw):
+    t = 0.0
+    while steps > 0:
+        (d, *_), us = _plan(n, n, L.LBM_F32_SHIFTED, steps, **kw)
+        t += us
+        steps -= d
+    return t
+
+
+@pytest.mark.parametrize("n,measured", [(700, 3.5), (1000, 6.3), (1400, 11.6), (2048, 26.8)])
+def test_tensor_rows_are_planned_as_one_workgroup_per_cu(n, measured):
+    """FP32 state with a tensor in FP64 arithmetic: the registers allow one
+    workgroup of the row kernel per CU. us per step as measured on the planned
+    launches, to 15%."""
+    t = _run_us(n, 600, perm=L.LBM_PERM_TENSOR) / 600
+    assert abs(t / measured - 1) < 0.15, t
