@@ -53,3 +53,26 @@ def test_state_after_a_non_finite_mean(nx, ny, dtype):
     want = _plain(nx, ny, dtype, 10, f)[0].cpu().numpy()
     assert np.array_equal(s.populations().cpu().numpy(), want, equal_nan=True)
     s.close()
+
+
+@pytest.mark.parametrize("nx,ny,dtype", [(2048, 1024, L.LBM_F32_SHIFTED), (1024, 1024, L.LBM_F64)])
+def test_a_converged_run_takes_no_step_beyond_its_last(nx, ny, dtype):
+    """A launch of a large grid costs far more than the idle time it would
+    fill: a run that converges at its second check leaves both population
+    buffers as a run of exactly those steps does."""
+    el, n = (8, nx * ny) if dtype == L.LBM_F64 else (4, nx * ny)
+    stride = (n + 63) // 64 * 64 * el + 16384
+    second = (9 * stride + 255) // 256 * 256
+
+    def buffers(s):
+        return [s.ws[o:o + 9 * stride].reshape(9, stride)[:, :n * el].clone() for o in (0, second)]
+
+    a, b = _solver(nx, ny, dtype), _solver(nx, ny, dtype)
+    st, done, _ = a.step(50, 0.9, 1)  # from rest the velocity doubles in the second step
+    assert (st, done) == (L.LBM_OK, 2)
+    for _ in range(2):
+        b.step(1, 0., 0, mean=False)
+    for x, y in zip(buffers(a), buffers(b)):
+        assert (x == y).all()
+    a.close()
+    b.close()
