@@ -33,6 +33,8 @@
 // types; FP32 storage only rounds the nine values written per cell.
 #include <hip/hip_runtime.h>
 
+#include <unistd.h>
+
 #include <chrono>
 #include <cmath>
 #include <cstring>
@@ -1547,6 +1549,25 @@ void field_check(const lbm_handle &h, const FieldRun &f, int64_t steps, bool fir
 
 }  // namespace
 
+namespace {
+
+// The status that run_to_steady_field's checks mirror to the host: 32 bytes of
+// pinned memory per thread that solves, kept from one solve to the next (freeing
+// pinned memory waits for every stream of the device, so a solve that freed its
+// own waited for unrelated work). A solve returns only once its stream is done, so
+// no two solves use one mirror at a time. Given back when the thread ends; the
+// main thread's goes with the process.
+struct HostMirror {
+    long long *p = nullptr;
+    ~HostMirror()
+    {
+        if (p && gettid() != getpid()) (void)hipHostFree(p);
+    }
+};
+thread_local HostMirror t_mirror;
+
+}  // namespace
+
 void fine_coef_planes(const lbm_params &p, char *ws, char **coef, char **force)
 {
     const Layout L = layout_of(&p);
@@ -1568,8 +1589,9 @@ lbm_status run_to_steady_field(const FieldRun &f, long long result[2])
     h.has_force = true;
     h.plan = plan_launches(h.p, true, std::max(1, device_cu_count()));
     const bool f64 = h.p.pop_dtype == LBM_F64;
-    long long *host = nullptr;
-    LBM_HIP(hipHostMalloc((void **)&host, 4 * sizeof(long long), hipHostMallocDefault));
+    if (!t_mirror.p)
+        LBM_HIP(hipHostMalloc((void **)&t_mirror.p, 4 * sizeof(long long), hipHostMallocPortable | hipHostMallocCoherent));
+    long long *host = t_mirror.p;
     host[0] = host[1] = host[2] = 0;
     hipError_t e = hipSuccess;
     const int n = h.p.nx * h.p.ny, nb = (n + kBlock - 1) / kBlock;
@@ -1598,8 +1620,9 @@ lbm_status run_to_steady_field(const FieldRun &f, long long result[2])
     if (e == hipSuccess) e = es;
     result[0] = host[0];
     result[1] = host[1];
-    (void)hipHostFree(host);
-    return e == hipSuccess ? LBM_OK : hip_check(e, "lbm_coarse_solve");
+    if (e == hipSuccess) return LBM_OK;
+    t_mirror.p = nullptr;  // a kernel of the failed solve may still store to it
+    return hip_check(e, "lbm_coarse_solve");
 }
 
 }  // namespace lbm
