@@ -464,16 +464,16 @@ __global__ __launch_bounds__(kBlock) void k_step(StepArgs<R> a)
 // writes f*_opp(a) to that same slot, and the step after reads its own slots
 // reversed and writes them in order again. A step's reads and writes touch the
 // same slots and no cell shares one, so a step needs one barrier and one copy
-// of the state. (The kernel before this one copied the state through
-// registers between two barriers, recomputed its cells' coordinates in every
-// step and, with a force or a tensor, read the coefficients from L2 in every
-// step.)
+// of the state. A cell reads its neighbours' slots only if it lies at least one
+// cell inside the halo tile, so every slot lies in its plane. (The kernel before
+// this one copied the state through registers between two barriers, recomputed
+// its cells' coordinates in every step and, with a force or a tensor, read the
+// coefficients from L2 in every step.)
 template <typename R>
 struct RegCoef {
     R v[4];
     __device__ R ld(int q, int) const { return v[q]; }
 };
-constexpr int kLdsPad = 72;  // elements before and after the LDS planes: the row above a tile's first cell
 __device__ constexpr int kOpp[9] = {0, 3, 4, 1, 2, 7, 8, 5, 6};
 
 // Any tile tx x ty whose halo tile fits BS x KM cells, any depth D >= 2. AXC: the
@@ -483,8 +483,7 @@ template <typename R, bool WALLS, int PK, bool FF, int BS, int KM, int AXC, type
 __global__ __launch_bounds__(BS) void k_tile(StepArgs<R> a, int D, int tx, int ty)
 {
     constexpr int CAP = BS * KM;
-    __shared__ R lds[8 * CAP + 2 * kLdsPad];
-    R *S = lds + kLdsPad;
+    __shared__ R S[8 * CAP];
     const int nx = a.nx, ny = a.ny;
     const int H = D - 1, AX = AXC ? AXC : tx + 2 * H;
     const int ntx = (nx + tx - 1) / tx;
@@ -640,7 +639,7 @@ __global__ __launch_bounds__(BS, WPE) void k_rows(StepArgs<float> a, int D)
     // FP32 arithmetic keeps 2E (the exact factor 2 of the collision)
     constexpr bool E2 = PK == 1 && !FF && sizeof(A) == 4;
     static_assert(GY || E2, "the variant without a y drive is the FP32 scalar one");
-    __shared__ R lds[8 * CAP + 2 * kLdsPad];
+    __shared__ R lds[8 * CAP];
     const int H = D - 1, tx = AX - 2 * H, ty = AY - 2 * H;
     const int nx = a.nx, ny = a.ny;
     const int ntx = (nx + tx - 1) / tx;
@@ -649,7 +648,7 @@ __global__ __launch_bounds__(BS, WPE) void k_rows(StepArgs<float> a, int D)
     const int x0 = (bid - tr * ntx) * tx, y0 = tr * ty;
     const int w1 = min(tx, nx - x0) + 2 * H, h1 = min(ty, ny - y0) + 2 * H;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    R *S = lds + kLdsPad + threadIdx.x;
+    R *S = lds + threadIdx.x;
     const int dcol = min(lane, w1 - 1 - lane);
     const bool interior = x0 >= H + 1 && x0 + w1 - H <= nx - 1 && y0 >= H + 1 && y0 + h1 - H <= ny - 1;
     auto body = [&](auto interior_tag) {
