@@ -471,7 +471,7 @@ extern "C" lbm_status lbm_coarse_solve(const lbm_params *fine, int32_t r, const 
             f.p.rho0 = 1.0;  // as the one-group kernel: deviations from 1
             f.ws = ws + L.off_fine;
             f.prev = ws + L.off_perm;
-            f.status = status;
+            f.done = reinterpret_cast<unsigned long long *>(status);
             f.tol = tol;
             f.check_every = check_every;
             f.max_steps = ms;

@@ -1004,20 +1004,22 @@ __global__ __launch_bounds__(kBlock) void k_rest(R *__restrict__ pops, int strid
 // Convergence of the whole velocity field (the coarse solve's test), taken on
 // the device: the fields of the current state, the relative L2 change of the
 // velocity since the last check (kept rounded to R), and, in the workgroup
-// that finishes last, the decision. status: [0] steps, [1] flag, [2] the run
-// has ended, [3] workgroups that are done; host mirrors [0..2]. Once the run has ended later checks leave everything as
-// it is, so steps may be queued past the end of the run before it is known.
+// that finishes last (done counts them, zero before and after), the decision.
+// host, pinned: [1] flag, [2] the run has ended, then [0] the steps, for which
+// the host waits. A check is queued only once the last one has been read, so
+// none runs after the end; the steps queued ahead of the reading do not change
+// the fields.
 template <typename R>
 __global__ __launch_bounds__(kBlock) void k_field_check(StepArgs<R> a, long long steps, bool first, double tol,
                                                         long long max_steps, R *__restrict__ prev,
                                                         double *__restrict__ partials, double *__restrict__ u_out,
-                                                        double *__restrict__ rho_out, long long *__restrict__ status,
+                                                        double *__restrict__ rho_out,
+                                                        unsigned long long *__restrict__ done,
                                                         long long *__restrict__ host)
 {
     __shared__ double red[2][kBlock / 64];
     __shared__ bool last;
     const int N = a.nx * a.ny, c = blockIdx.x * kBlock + threadIdx.x;
-    if (!first && status[2] != 0) return;
     double d2 = 0.0, u2 = 0.0;
     if (c < N) {
         R fr[9];
@@ -1058,9 +1060,7 @@ __global__ __launch_bounds__(kBlock) void k_field_check(StepArgs<R> a, long long
         // device-wide visible before the count says so
         __hip_atomic_store(&partials[2 * blockIdx.x], sd, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __hip_atomic_store(&partials[2 * blockIdx.x + 1], su, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const unsigned long long done = __hip_atomic_fetch_add(reinterpret_cast<unsigned long long *>(&status[3]), 1ull,
-                                                               __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
-        last = done == gridDim.x - 1;
+        last = __hip_atomic_fetch_add(done, 1ull, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1;
     }
     __syncthreads();
     if (!last || threadIdx.x >= 64) return;
@@ -1084,10 +1084,7 @@ __global__ __launch_bounds__(kBlock) void k_field_check(StepArgs<R> a, long long
     if (!isfinite(td) || !isfinite(tu)) flag = 2;
     else if (!first && tol > 0.0 && sqrt(td) <= tol * sqrt(tu)) flag = 0;
     else if (steps >= max_steps) flag = tol > 0.0 ? 1 : 0;
-    status[0] = steps;
-    status[1] = flag;
-    status[2] = flag >= 0;
-    status[3] = 0;
+    *done = 0;
     host[1] = flag;
     host[2] = flag >= 0;
     __hip_atomic_store(&host[0], steps, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
@@ -1543,7 +1540,7 @@ void field_check(const lbm_handle &h, const FieldRun &f, int64_t steps, bool fir
     const int n = h.p.nx * h.p.ny;
     hipLaunchKernelGGL(k_field_check<R>, dim3((n + kBlock - 1) / kBlock), dim3(kBlock), 0, h.stream, step_args<R>(&h),
                        (long long)steps, first, f.tol, (long long)f.max_steps, reinterpret_cast<R *>(f.prev),
-                       reinterpret_cast<double *>(h.ws + h.L.off_part), f.u, f.rho, f.status, host);
+                       reinterpret_cast<double *>(h.ws + h.L.off_part), f.u, f.rho, f.done, host);
 }
 
 }  // namespace
@@ -1594,7 +1591,7 @@ lbm_status run_to_steady_field(const FieldRun &f, long long result[2])
     host[0] = host[1] = host[2] = 0;
     hipError_t e = hipSuccess;
     const int n = h.p.nx * h.p.ny, nb = (n + kBlock - 1) / kBlock;
-    hipLaunchKernelGGL(k_zero_i32, dim3(1), dim3(64), 0, f.stream, reinterpret_cast<int *>(f.status), 8);
+    hipLaunchKernelGGL(k_zero_i32, dim3(1), dim3(64), 0, f.stream, reinterpret_cast<int *>(f.done), 2);
     if (f64)
         hipLaunchKernelGGL(k_rest<double>, dim3(nb), dim3(kBlock), 0, f.stream,
                            reinterpret_cast<double *>(h.ws + h.L.off_a), (int)h.L.stride, n);

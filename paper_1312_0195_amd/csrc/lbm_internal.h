@@ -65,7 +65,7 @@ struct FieldRun {
     lbm_params p;
     char *ws;              // a fine-grid workspace for p, its coefficient planes filled
     void *prev;            // 2 n values of the population type
-    long long *status;     // 4 device values
+    unsigned long long *done;  // a device counter
     double tol;
     int check_every;
     int64_t max_steps;     // a multiple of check_every
