@@ -48,3 +48,30 @@ def test_tensor_rows_are_planned_as_one_workgroup_per_cu(n, measured):
     launches, to 15%."""
     t = _run_us(n, 600, perm=L.LBM_PERM_TENSOR) / 600
     assert abs(t / measured - 1) < 0.15, t
+
+
+# grids that test_gpu_planned_kernels.py steps, with the tile that each plans:
+# narrower than a tile and its halo, runs of two planes, last runs of one, and
+# several ragged columns
+D3Q19_GRIDS = {L.LBM_F32_SHIFTED: [((63, 33, 101), (64, 8, 2)), ((61, 2001, 2), (64, 8, 2)),
+                                   ((130, 90, 75), (64, 8, 11)), ((15, 501, 31), (16, 8, 3)),
+                                   ((31, 131, 67), (16, 8, 3)), ((130, 129, 130), (16, 8, 33))],
+               L.LBM_F64: [((63, 501, 5), (64, 4, 3)), ((61, 1001, 2), (64, 4, 2)), ((191, 9, 131), (64, 4, 5)),
+                           ((128, 128, 128), (64, 4, 32)), ((15, 1001, 5), (16, 8, 2)), ((9, 2001, 4), (16, 8, 2)),
+                           ((130, 7, 101), (16, 8, 2))]}
+
+
+def test_the_d3q19_grids_reach_every_tile():
+    for dtype, grids in D3Q19_GRIDS.items():
+        for n, tile in grids:
+            assert _plan3(*n, dtype) == (2, *tile), n
+
+
+# stretches over which a 1030 x 777 grid with a drive along x only and FP32
+# arithmetic takes the row kernels: 64 x 36 and 64 x 32 halo tiles
+ROW_GRID, ROW_STRETCHES = (1030, 777), (2, 3, 4, 5, 6, 7, 8, 13)
+
+
+def test_the_row_grid_reaches_both_row_kernels():
+    kernels = [_plan(*ROW_GRID, L.LBM_F32_FAST, n, gy=0.0)[0][1] for n in ROW_STRETCHES]
+    assert set(kernels) == {4, 5}
