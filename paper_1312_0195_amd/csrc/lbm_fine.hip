@@ -1489,7 +1489,7 @@ void queue_mean(lbm_handle *h)
 // device: the host looks for the value itself for up to 5 ms, beside which the
 // 10 us that an idle device loses are little, then waits for the stream.
 // 64 x 64 cells, a check every 100 steps: 80 us per interval, 90 with a copy
-// and a synchronisation.
+// and a synchronisation (75 now that the steps take less).
 hipError_t wait_value(const void *at, unsigned long long value, hipStream_t stream)
 {
     const auto *p = static_cast<const unsigned long long *>(at);
@@ -1751,9 +1751,10 @@ extern "C" lbm_status lbm_step(lbm_handle *h, int64_t max_steps, double tol, int
     // which the device waits for the host. With a tolerance any check may be the
     // last, and the launch is then waited for in vain, so it is queued once the
     // call's checks together have idled for as long as it takes: at once where a
-    // launch takes 7 us (64 x 64 cells), never within the first 46 checks at
-    // 4096 x 4096 (0.47 ms). A run so never pays more for its end than its checks
-    // have cost it.
+    // launch takes 7 us (64 x 64 cells), not within the first 42 checks at
+    // 4096 x 4096 (0.43 ms). So a run never pays more for its end than its checks
+    // have cost it; two intervals of 12 steps that end in convergence take
+    // 2050 us at 4096 x 4096, and took 2440 with the launch always queued.
     auto depth = [&] {
         const int64_t to_check = check_every > 0 ? check_every - done % check_every : max_steps - done;
         return launch_depth(h->plan, std::min<int64_t>(to_check, max_steps - done));
