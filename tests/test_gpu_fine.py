@@ -150,6 +150,10 @@ def test_fine_converges_to_oracle_steady_state(L):
         assert _rel_field_err(u.cpu().numpy(), np.stack([uxo, uyo])) < 10 * tol_u
 
 
+# The steps per launch named in the multi-step tests below are those of earlier
+# kernels. A launch now takes up to twelve, on a kernel and tile planned per grid:
+# test_launch_plans.py holds plans, test_gpu_planned_kernels.py and
+# test_gpu_launch_plan.py compare every kernel.
 @pytest.mark.parametrize("nx,ny,walls", [(2048, 96, 1), (130, 70, 0), (200, 37, 1), (64, 33, 1),
                                          (5, 3, 0), (3, 40, 1)])
 @pytest.mark.parametrize("dtype", ["f32", "f64", "f32_fast"])
