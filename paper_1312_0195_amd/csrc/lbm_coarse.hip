@@ -15,12 +15,13 @@
 // cells per thread, with the in-place streaming of the local solver takes every
 // step without a launch. From there to 4096 cells (FP64 state 2048) the fine
 // grid's many-step launches run the lattice on all CUs, and the same
-// convergence test on the velocity field is taken on the device. Larger coarse
+// convergence test on the velocity field is taken on the device; with few steps
+// between checks the one workgroup stays the faster (in_one_group). Larger coarse
 // grids are a fine-grid solve with a tensor permeability (its own test, on the
-// mean velocity). us per step with FP32 / FP64 state: 8 x 8 0.57 / 0.24 ->
-// 0.24 / 0.21, 32 x 32 1.65 / 0.61 -> 0.62 / 0.57, 45 x 45 2.50 / 1.19 ->
-// 0.83 / 0.81, 64 x 64 3.5 -> 0.82; before, one workgroup ran up to four cells
-// per thread. The line between the first two: at 40 x 40 one workgroup takes
+// mean velocity). us per step with FP32 / FP64 state, a check every 100: 8 x 8
+// 0.57 / 0.24 -> 0.24 / 0.21, 32 x 32 1.65 / 0.61 -> 0.62 / 0.57, 45 x 45 2.50 /
+// 1.19 -> 0.83 / 0.81, 64 x 64 3.5 -> 0.82; before, one workgroup ran up to four
+// cells per thread. The line between the first two: at 40 x 40 one workgroup takes
 // 0.9 us per step, the launches 0.8 and 0.1 ms more per solve.
 #include <hip/hip_runtime.h>
 
@@ -34,7 +35,7 @@
 namespace lbm {
 namespace {
 
-constexpr int kOneGroup = 1664;  // cells of the largest grid one workgroup runs
+constexpr int kOneGroup = 1664;  // cells up to which one workgroup runs every solve
 // cells up to which the convergence test is on the velocity field
 constexpr int kField32 = 4096, kField64 = 2048;
 
@@ -318,8 +319,23 @@ __global__ __launch_bounds__(256) void k_block_average(const double *__restrict_
     if (threadIdx.x == 0) out[o] = ((red[0] + red[1]) + (red[2] + red[3])) / ((double)r * r);
 }
 
+// Whether one workgroup takes the whole solve. Beyond kOneGroup cells the launches
+// pay for each check: an interval of m steps takes at least 12 us (launches, the
+// check, its trip to the host), 5.9 + 0.8 m where the steps set it; one workgroup
+// takes 2.5 us for the check and for a step 0.62 ns per cell with two cells per
+// thread, 0.64 with three and 1.15 with four. us per step at m = 2 / 4 / 8 / 16:
+// 45 x 45 FP64 2.4 / 1.8 / 1.5 / 1.3 in one workgroup, 6.0 / 3.1 / 1.6 / 1.2 in
+// launches; 55 x 55 3.9 / 2.9 / 2.4 / 2.1 and 6.2 / 3.2 / 1.7 / 1.25.
+bool in_one_group(int n, bool f64, int check_every)
+{
+    if (n <= kOneGroup) return true;
+    if (n > (f64 ? kField64 : kField32)) return false;
+    const double m = check_every, step = n * (n <= 2048 ? 0.62e-3 : n <= 3072 ? 0.64e-3 : 1.15e-3);
+    return 2.5 + m * step <= std::max(12.0 + 0.15 * m, 5.9 + 0.8 * m);
+}
+
 struct CoarseLayout {
-    bool one_group, field;  // one workgroup; else the test on the field
+    bool field;  // the test on the field
     size_t off_M, off_heg, off_status, off_flag, off_perm, off_force, off_fine, fine_bytes, total;
 };
 
@@ -327,7 +343,6 @@ CoarseLayout coarse_layout(int ncx, int ncy, bool f64)
 {
     CoarseLayout L{};
     const size_t n = (size_t)ncx * ncy;
-    L.one_group = n <= (size_t)kOneGroup;
     L.field = n <= (size_t)(f64 ? kField64 : kField32);
     size_t off = 0;
     L.off_M = off;      off = align_up(off + 4 * n * sizeof(double));
@@ -372,8 +387,14 @@ lbm_status launch_onchip(const lbm_params &pc, char *ws, const CoarseLayout &L, 
         hipLaunchKernelGGL((k_coarse_onchip<R, 256, 1>), dim3(1), dim3(256), 0, stream, a);
     else if (n <= 1024)
         hipLaunchKernelGGL((k_coarse_onchip<R, 1024, 1>), dim3(1), dim3(1024), 0, stream, a);
-    else
+    else if (n <= 2048)
         hipLaunchKernelGGL((k_coarse_onchip<R, 1024, 2>), dim3(1), dim3(1024), 0, stream, a);
+    if constexpr (sizeof(R) == 4) {  // FP64 planes of more cells do not fit LDS
+        if (n > 3072)
+            hipLaunchKernelGGL((k_coarse_onchip<R, 1024, 4>), dim3(1), dim3(1024), 0, stream, a);
+        else if (n > 2048)
+            hipLaunchKernelGGL((k_coarse_onchip<R, 1024, 3>), dim3(1), dim3(1024), 0, stream, a);
+    }
     LBM_HIP(hipGetLastError());
     return LBM_OK;
 }
@@ -424,6 +445,7 @@ extern "C" lbm_status lbm_coarse_solve(const lbm_params *fine, int32_t r, const 
     const int ncx = pc.nx, ncy = pc.ny, n = ncx * ncy;
     const bool f64 = fine->pop_dtype == LBM_F64;
     const CoarseLayout L = coarse_layout(ncx, ncy, f64);
+    const bool one_group = in_one_group(n, f64, check_every);
     const size_t need = L.total;
     if (!d_ws || ((uintptr_t)d_ws % kAlign) != 0 || ws_bytes < need)
         return set_error(LBM_EWORKSPACE, fn + "workspace NULL, misaligned or smaller than " + std::to_string(need));
@@ -439,7 +461,7 @@ extern "C" lbm_status lbm_coarse_solve(const lbm_params *fine, int32_t r, const 
     const dim3 cg((n + 255) / 256), cb(256);
     // the coefficients go where the path that uses them reads them
     char *coef = ws + L.off_M, *heg = ws + L.off_heg;
-    if (L.field && !L.one_group) fine_coef_planes(pc, ws + L.off_fine, &coef, &heg);
+    if (L.field && !one_group) fine_coef_planes(pc, ws + L.off_fine, &coef, &heg);
     double *pp = L.field ? nullptr : perm_c, *fp = L.field ? nullptr : force_c;
     if (f64)
         hipLaunchKernelGGL(k_coarse_coef<double>, cg, cb, 0, stream, d_keff, d_force, n, tensor, (double)r, pc.eps, pc.nu,
@@ -454,7 +476,7 @@ extern "C" lbm_status lbm_coarse_solve(const lbm_params *fine, int32_t r, const 
     const int64_t ms = std::min<int64_t>((max_steps + check_every - 1) / check_every * check_every, (int64_t)1 << 30);
     long long result[2] = {0, 0};
     int bad = 0;
-    if (L.one_group) {
+    if (one_group) {
         // the permeability check is read back with the result: with a bad one the kernel leaves at once
         const lbm_status ls = f64 ? launch_onchip<double>(pc, ws, L, tol, check_every, ms, d_u, d_rho, stream)
                                   : launch_onchip<float>(pc, ws, L, tol, check_every, ms, d_u, d_rho, stream);
@@ -465,7 +487,7 @@ extern "C" lbm_status lbm_coarse_solve(const lbm_params *fine, int32_t r, const 
     LBM_HIP(hipStreamSynchronize(stream));
     if (bad) return set_error(LBM_EINVAL, fn + "effective permeability must be positive definite");
     if (L.field) {
-        if (!L.one_group) {
+        if (!one_group) {
             FieldRun f{};
             f.p = pc;
             f.p.rho0 = 1.0;  // as the one-group kernel: deviations from 1

@@ -68,3 +68,49 @@ def test_bad_permeability_is_refused_in_every_range(L):
         with pytest.raises(L.LbmError) as e:
             L.lbm_coarse_solve(fine, 8, torch.as_tensor(K).cuda(), 1, None, 130, 1e-6, 50, u, None, ws, nb)
         assert e.value.status == L.LBM_EINVAL
+
+
+@pytest.mark.parametrize("ncx,ncy,dtype", [(41, 41, 0), (64, 32, 0), (64, 32, 1), (46, 45, 0), (51, 60, 0), (64, 48, 0),
+                                           (60, 60, 0), (64, 64, 0)])
+def test_any_check_interval_takes_the_same_steps(L, ncx, ncy, dtype):
+    """Few steps between checks run in one workgroup, more of them in launches
+    on all CUs: the same 60 steps bit for bit."""
+    rng = np.random.default_rng(ncx)
+    k = np.exp(0.6 * rng.standard_normal((ncy, ncx)))
+    K = torch.as_tensor(np.stack([k, 0.2 * k, 0.1 * k, 0.5 + k[::-1, ::-1]], axis=-1)).cuda()
+    fine = L.make_params(ncx * 8, ncy * 8, 0.8, 0.4, 0.1, 1.0, 1e-6, 3e-7, 0, dtype)
+    nb = L.lbm_coarse_workspace_bytes(ncx, ncy)
+    ws = torch.empty(nb, dtype=torch.uint8, device="cuda")
+    got = []
+    for every in (60, 2, 4, 6, 10, 12, 20):
+        u = torch.full((2, ncy, ncx), float("nan"), dtype=torch.float64, device="cuda")
+        rho = torch.full((ncy, ncx), float("nan"), dtype=torch.float64, device="cuda")
+        st, steps = L.lbm_coarse_solve(fine, 8, K, L.LBM_KEFF_TENSOR, None, 60, 0.0, every, u, rho, ws, nb)
+        assert (st, steps) == (L.LBM_OK, 60)
+        got.append((every, u, rho))
+    for every, u, rho in got[1:]:
+        assert torch.equal(u, got[0][1]) and torch.equal(rho, got[0][2]), every
+    assert float(got[0][1].abs().max()) > 0
+
+
+@pytest.mark.parametrize("n,dtype", [(45, 1), (46, 0)])
+def test_frequent_checks_do_not_pay_a_round_trip_each(L, n, dtype):
+    """A check every two steps against one every 50, the same steps: 2.8 (45 x
+    45, two cells per thread) and 3.5 (46 x 46) times the time in one workgroup,
+    6.8 with the host waiting for each check."""
+    import time
+    K = torch.as_tensor(np.tile(np.array([1.0, 0.1, 0.1, 0.8]), (n, n, 1))).cuda()
+    fine = L.make_params(n * 8, n * 8, 0.8, 0.4, 0.1, 1.0, 1e-6, 0.0, 0, dtype)
+    nb = L.lbm_coarse_workspace_bytes(n, n)
+    ws = torch.empty(nb, dtype=torch.uint8, device="cuda")
+    u = torch.empty((2, n, n), dtype=torch.float64, device="cuda")
+    t = {}
+    for every in (50, 2):
+        runs = []
+        for _ in range(7):
+            torch.cuda.synchronize()
+            t0 = time.perf_counter()
+            L.lbm_coarse_solve(fine, 8, K, L.LBM_KEFF_TENSOR, None, 1000, 0.0, every, u, None, ws, nb)
+            runs.append(time.perf_counter() - t0)
+        t[every] = sorted(runs)[3]
+    assert t[2] < 5.0 * t[50], t
