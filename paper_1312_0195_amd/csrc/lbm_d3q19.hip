@@ -676,6 +676,14 @@ void launch_fields(const lbm3d_handle *h, double *u, double *rho, double *part)
 //     256 MB last-level cache, 4.5 TB/s beyond;
 //   a single step: 2.2 us + its bytes at 5.2 to 8.5 TB/s, more where rows leave
 //     lanes idle.
+// Grids of up to four planes (thin) in one run: the two planes below and above are
+// read but not stored and count as one (as two where the caches hold the state and
+// a lone workgroup per CU waits for its reads), and between walls there are none.
+// Such launches are short enough that a launch's own 2.8 us show. Measured over 38
+// grids of 1 to 4 planes, us per step before (as thick grids) and now: FP32 1500 x
+// 1500 x 2 151 and 128 (walls 153 and 108), 256 x 256 x 1 with walls 4.2 and 2.8,
+// 70 x 70 x 4 4.0 and 3.2; FP64 700 x 700 x 2 61 and 54, 1500 x 1500 x 2 with walls
+// 298 and 174; none slower by more than 3%.
 // Measured (us per step; before, FP32 state always took two steps on 64 x 8 tiles
 // and FP64 state single steps): FP32 24^3 14.5 -> 3.2 (single steps),
 // 64^3 14.3 -> 7.5 (64 x 8, runs of 2 planes), 30 x 200 x 40 15.3 -> 8.3 (16 x 8),
@@ -702,7 +710,8 @@ void plan_steps(const lbm3d_params &p, int64_t cus, int *shape, int *zchunk)
     const bool cached = bytes < 240e6;
     const double lanes = (double)p.nx / (kTX * ((p.nx + kTX - 1) / kTX));
     const double one = bytes < 64e6 ? 8.5e6 : bytes < 150e6 ? 7.5e6 : cached ? 7.0e6 : 5.2e6;  // bytes per us
-    double best = 2.0 * (2.2 + bytes / one * (1.0 + 0.7 * (1.0 - lanes)));
+    const bool thin = p.nz <= 4;
+    double best = 2.0 * ((thin ? 2.8 : 2.2) + bytes / one * (1.0 + 0.7 * (1.0 - lanes)));
     *shape = kSingle;
     *zchunk = 1;
     for (int t = 0; t < kTiles; ++t) {
@@ -712,7 +721,7 @@ void plan_steps(const lbm3d_params &p, int64_t cus, int *shape, int *zchunk)
         const int64_t slots = cus * ti.resident;
         // every number of runs once, each with its shortest: about 2 sqrt(nz) of them (trying each
         // number up to nz took 9 ms for a column of a million planes)
-        for (int zc = p.nz; zc >= 2; --zc) {
+        for (int zc = p.nz; zc >= std::min(p.nz, 2); --zc) {
             const int runs = (p.nz - 1) / zc + 1;
             zc = (p.nz - 1) / runs + 1;
             const int64_t wgs = cols * runs;
@@ -721,7 +730,10 @@ void plan_steps(const lbm3d_params &p, int64_t cus, int *shape, int *zchunk)
             // (small workgroups that share a CU also lengthen each other's chains)
             const double share = ti.resident == 4 ? 0.4 * std::ceil((double)std::min(wgs, slots) / (double)cus) : 0.0;
             const double plane = std::max(ti.chain[!cached] + share, moved / (cached ? 6.6e6 : 4.5e6));
-            const double us = 3.5 + rounds * (zc + 2) * plane;
+            const double halo = !(thin && runs == 1) ? 2.0
+                                : ti.resident == 1   ? (p.walls_z ? 0.6 : cached ? 2.0 : 1.2)
+                                                     : (p.walls_z ? 0.0 : 1.0);
+            const double us = 3.5 + rounds * (zc + halo) * plane;
             if (us < best) {
                 best = us;
                 *shape = t;

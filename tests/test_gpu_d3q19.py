@@ -70,8 +70,8 @@ def test_steps_from_rest_match_oracle(L, shape, walls, dtype):
     s.close()
 
 
-# These shapes plan single steps by now, in both calls of the test below; narrow
-# grids and runs of one or two planes on the two-step kernel are in
+# Most of these shapes plan single steps by now, in both calls of the test below;
+# narrow grids and runs of one or two planes on the two-step kernel are in
 # test_gpu_planned_kernels.py.
 @pytest.mark.parametrize("shape", [(70, 9, 70), (40, 17, 33), (5, 3, 1), (1, 1, 3), (33, 8, 2),
                                    (64, 16, 32)])

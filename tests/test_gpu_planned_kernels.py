@@ -4,7 +4,7 @@ them."""
 import numpy as np
 import pytest
 
-from test_launch_plans import D3Q19_GRIDS, ROW_GRID, ROW_STRETCHES
+from test_launch_plans import D3Q19_GRIDS, ROW_GRID, ROW_STRETCHES, THIN_GRIDS
 
 pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
@@ -32,6 +32,11 @@ def test_d3q19_two_step_tiles_equal_single_steps(L, dtype, n, walls):
     assert float((fa[1] - fa[2]).abs().max()) > 0
     a.close()
     b.close()
+
+
+@pytest.mark.parametrize("dtype,walls,n", [(d, w, n) for (d, w), grids in THIN_GRIDS.items() for n in grids])
+def test_d3q19_thin_grids_equal_single_steps(L, dtype, walls, n):
+    test_d3q19_two_step_tiles_equal_single_steps(L, dtype, n, walls)
 
 
 @pytest.mark.parametrize("walls", [0, 1])

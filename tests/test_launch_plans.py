@@ -56,7 +56,7 @@ def test_tensor_rows_are_planned_as_one_workgroup_per_cu(n, measured):
 D3Q19_GRIDS = {L.LBM_F32_SHIFTED: [((63, 33, 101), (64, 8, 2)), ((61, 2001, 2), (64, 8, 2)),
                                    ((130, 90, 75), (64, 8, 11)), ((15, 501, 31), (16, 8, 3)),
                                    ((31, 131, 67), (16, 8, 3)), ((130, 129, 130), (16, 8, 33))],
-               L.LBM_F64: [((63, 501, 5), (64, 4, 3)), ((61, 1001, 2), (64, 4, 2)), ((191, 9, 131), (64, 4, 5)),
+               L.LBM_F64: [((63, 501, 5), (64, 4, 3)), ((703, 699, 2), (64, 4, 2)), ((191, 9, 131), (64, 4, 5)),
                            ((128, 128, 128), (64, 4, 32)), ((15, 1001, 5), (16, 8, 2)), ((9, 2001, 4), (16, 8, 2)),
                            ((130, 7, 101), (16, 8, 2))]}
 
@@ -75,3 +75,18 @@ ROW_GRID, ROW_STRETCHES = (1030, 777), (2, 3, 4, 5, 6, 7, 8, 13)
 def test_the_row_grid_reaches_both_row_kernels():
     kernels = [_plan(*ROW_GRID, L.LBM_F32_FAST, n, gy=0.0)[0][1] for n in ROW_STRETCHES]
     assert set(kernels) == {4, 5}
+
+
+# thin grids that take two steps per launch, with walls in z or without
+THIN_GRIDS = {(L.LBM_F32_SHIFTED, 0): [(1500, 700, 2), (301, 299, 2)],
+              (L.LBM_F32_SHIFTED, 1): [(61, 67, 1), (255, 130, 1), (1999, 1001, 1), (301, 299, 2), (1500, 700, 2),
+                                       (1201, 401, 3)],
+              (L.LBM_F64, 0): [(703, 699, 2), (500, 501, 3)],
+              (L.LBM_F64, 1): [(61, 67, 1), (255, 130, 1), (703, 1001, 1), (301, 299, 2), (500, 301, 4)]}
+
+
+def test_thin_grids_take_two_steps_per_launch():
+    for (dtype, walls), grids in THIN_GRIDS.items():
+        for n in grids:
+            steps, _, _, zc = _plan3(*n, dtype, walls)
+            assert (steps, zc) == (2, n[2]), (n, dtype, walls)
