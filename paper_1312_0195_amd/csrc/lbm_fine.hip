@@ -1409,6 +1409,40 @@ double launch_us(const lbm_params &p, bool force, int cus, int shape, int D, int
     return 2.7 + rounds * t + (double)p.nx * p.ny * planes * (f64 ? 8.0 : 4.0) / 8.0e6;
 }
 
+// Launches of few steps on grids that fill the device are bound by the state's
+// way through memory, which the model above adds to the steps' time instead of
+// overlapping them. Where that misleads it their tiles come from measurements of 26
+// grids from 200^2 to 4096^2, all types and coefficients (us of a launch, the
+// model's choice and this one). Two steps of a state that the caches hold: tiles of
+// 512 threads, several per CU, 30 x 14 for FP64 arithmetic on FP32 state, else 62 x
+// 6, up to 850 000 cells (512^2 13.7 and 6.7, 700 x 500 9.1 and 7.7, with FP32
+// arithmetic 8.9 and 6.3), above that where the model's rows need a second round
+// for a few tiles (1024^2 17.6 and 16.0), and for a tensor, whose rows fill a CU with
+// one workgroup (1024^2 24.7 and 18.5). Beyond the caches, for FP64 state, tensors
+// and from 5 000 000 cells: 62 x 14 tiles of 1024 threads (2048^2 FP64 154 and 131,
+// 4096^2 FP32 302 and 268). Three and four steps with a tensor: 60 x 12 and 58 x 10 of
+// them (1024^2, four steps, 32.3 and 26.9).
+// The time handed to the plan is the larger of both predictions, so that longer
+// stretches are planned as before. us 0: the model's choice stands.
+Launch few_steps(const lbm_params &p, bool force, int cus, int D)
+{
+    const double cells = (double)p.nx * p.ny, el = p.pop_dtype == LBM_F64 ? 8.0 : 4.0;
+    const bool f32 = p.pop_dtype == LBM_F32_SHIFTED, tensor = f32 && p.perm_kind == LBM_PERM_TENSOR;
+    const bool cached = 18.0 * cells * el < 240e6;
+    const int rows = ((p.nx + 61) / 62) * ((p.ny + 33) / 34);  // tiles of the row kernel at two steps
+    const bool sc = p.scheme == LBM_SCHEME_SHAN_CHEN;
+    const bool second = f32 && sc && rows > 2 * cus && rows < 4 * cus && cells < 1.75e6;
+    const bool small = D == 2 && cached && cells >= 40e3 && (cells < 850e3 || tensor || second);
+    const bool large = (D == 2 && !cached && (el == 8.0 || tensor || (sc && cells > 5e6))) ||
+                       (D > 2 && D <= 4 && tensor && cells >= 500e3);
+    if (p.nx < 64 || p.ny < 128 || !(small || large)) return Launch{};
+    const int h2 = 2 * (D - 1), w = (small && f32 ? 32 : 64) - h2;
+    const int columns = (p.nx + w - 1) / w, tx = (p.nx + columns - 1) / columns;
+    const int ty = (small ? 512 : 1024) / (tx + h2) - h2;
+    const double bytes = cells * el * (19.0 + (force ? 2.0 : 0.0) + (p.perm_kind == LBM_PERM_TENSOR ? 3.0 : 0.0));
+    return Launch{small ? kTile512 : kTile1024, tx, ty, 3.0 + bytes / (small ? 6.4e6 : 4.75e6)};
+}
+
 // Per depth, the shape and tile of least predicted time; then the sequence of
 // depths that covers a stretch of up to kPlanRoom steps in the least time
 // (longer stretches start with the depth of least time per step). Every depth
@@ -1430,8 +1464,11 @@ Plan plan_launches(const lbm_params &p, bool force, int cus)
         };
         const int h2 = 2 * (D - 1);
         const int cap[3] = {512, 1024, 2048}, shape[3] = {kTile512, kTile1024, kTile2048};
+        // rows of fewer than 16 cells read partial cache lines, which few steps do not
+        // make up for (300^2, three steps: 6 x 75 tiles 6.3 us, 58 x 12 5.6)
+        const int narrowest = D <= 5 && p.nx >= 64 && (double)p.nx * p.ny >= 40e3 ? 16 : 4;
         for (int i = 0; i < 3; ++i)
-            for (int w = 4, last = 0; w <= 64 && w + h2 <= cap[i]; ++w) {
+            for (int w = narrowest, last = 0; w <= 64 && w + h2 <= cap[i]; ++w) {
                 const int tx = (p.nx + (p.nx + w - 1) / w - 1) / ((p.nx + w - 1) / w);  // even columns of tiles
                 if (tx == last) continue;
                 last = tx;
@@ -1443,7 +1480,8 @@ Plan plan_launches(const lbm_params &p, bool force, int cus)
         if (f64 && D <= 10) offer(kTile32, 32 - h2, 32 - h2);
         if (!f64 && D <= 10) offer(kRows768, 64 - h2, 36 - h2);
         if (fast && D <= 10) offer(kRows1024, 64 - h2, 32 - h2);
-        pl.at[D] = best;
+        const Launch few = few_steps(p, force, cus, D);
+        pl.at[D] = few.us > 0.0 ? Launch{few.shape, few.tx, few.ty, std::max(few.us, best.us)} : best;
     }
     const double el = f64 ? 8.0 : 4.0;
     pl.at[1].us = 2.7 + (double)p.nx * p.ny * 19.0 * el / 5.0e6;

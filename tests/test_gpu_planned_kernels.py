@@ -4,7 +4,7 @@ them."""
 import numpy as np
 import pytest
 
-from test_launch_plans import D3Q19_GRIDS, ROW_GRID, ROW_STRETCHES, THIN_GRIDS
+from test_launch_plans import D3Q19_GRIDS, FEW_GRIDS, FORMS, ROW_GRID, ROW_STRETCHES, THIN_GRIDS
 
 pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
@@ -56,26 +56,32 @@ def test_rows_with_a_drive_along_x_only_equal_single_steps(L, walls):
     b.close()
 
 
-@pytest.mark.parametrize("dtype,force,perm,scheme", [(0, 0, 1, 0), (0, 1, 1, 0), (0, 0, 4, 0), (0, 1, 4, 0), (0, 0, 1, 1),
-                                                     (0, 1, 1, 1), (1, 0, 1, 0), (1, 1, 4, 0), (1, 0, 1, 1), (2, 0, 1, 0),
-                                                     (2, 1, 1, 0), (2, 0, 4, 0), (2, 1, 4, 0)])
-def test_large_walled_grids_equal_single_steps(L, dtype, force, perm, scheme):
-    """The kernels of large grids between walls, where the edge tiles bounce
-    back in LDS."""
-    nx, ny = ROW_GRID
+def _equal_single_steps(L, nx, ny, walls, stretches, dtype, force, perm, scheme):
     rng = np.random.default_rng(8)
     k = np.exp(rng.standard_normal((ny, nx)))
     if perm == L.LBM_PERM_TENSOR:
         off = 0.2 * np.minimum(k, k[::-1])
         k = np.stack([k, off, 0.5 * off, k[::-1]], axis=-1)
     g = 1e-6 * rng.standard_normal((ny, nx, 2)) if force else None
-    p = L.make_params(nx, ny, 0.8, 0.4, 0.1, 1.0, 1e-6, 3e-7, 1, dtype, perm, scheme)
+    p = L.make_params(nx, ny, 0.8, 0.4, 0.1, 1.0, 1e-6, 3e-7, walls, dtype, perm, scheme)
     a, b = L.FineSolver(p, k, g), L.FineSolver(p, k, g)
-    total = sum(ROW_STRETCHES)
-    for n in ROW_STRETCHES:
+    for n in stretches:
         a.step(n, mean=False)
-    for _ in range(total):
+    for _ in range(sum(stretches)):
         b.step(1, mean=False)
     assert torch.equal(a.populations(), b.populations())
     a.close()
     b.close()
+
+
+@pytest.mark.parametrize("dtype,force,perm,scheme", FORMS)
+def test_large_walled_grids_equal_single_steps(L, dtype, force, perm, scheme):
+    """The kernels of large grids between walls, where the edge tiles bounce
+    back in LDS."""
+    _equal_single_steps(L, *ROW_GRID, 1, ROW_STRETCHES, dtype, force, perm, scheme)
+
+
+@pytest.mark.parametrize("nx,ny", FEW_GRIDS)
+@pytest.mark.parametrize("dtype,force,perm,scheme", FORMS)
+def test_few_steps_equal_single_steps(L, nx, ny, dtype, force, perm, scheme):
+    _equal_single_steps(L, nx, ny, (nx + dtype) % 2, (2, 3, 4), dtype, force, perm, scheme)

@@ -74,7 +74,7 @@ ROW_GRID, ROW_STRETCHES = (1030, 777), (2, 3, 4, 5, 6, 7, 8, 13)
 
 def test_the_row_grid_reaches_both_row_kernels():
     kernels = [_plan(*ROW_GRID, L.LBM_F32_FAST, n, gy=0.0)[0][1] for n in ROW_STRETCHES]
-    assert set(kernels) == {4, 5}
+    assert {4, 5} <= set(kernels)
 
 
 # thin grids that take two steps per launch, with walls in z or without
@@ -90,3 +90,28 @@ def test_thin_grids_take_two_steps_per_launch():
         for n in grids:
             steps, _, _, zc = _plan3(*n, dtype, walls)
             assert (steps, zc) == (2, n[2]), (n, dtype, walls)
+
+
+FORMS = [(0, 0, 1, 0), (0, 1, 1, 0), (0, 0, 4, 0), (0, 1, 4, 0), (0, 0, 1, 1), (0, 1, 1, 1), (1, 0, 1, 0), (1, 1, 4, 0),
+         (1, 0, 1, 1), (2, 0, 1, 0), (2, 1, 1, 0), (2, 0, 4, 0), (2, 1, 4, 0)]  # type, force, perm, scheme
+
+
+def test_few_steps_do_not_run_on_slivers():
+    """Rows of a few cells read partial cache lines: a two-step launch of 512^2
+    cells on tiles of 4 x 256 took twice the time of one on 30 x 14."""
+    for dtype, force, perm, scheme in FORMS:
+        for n in (200, 256, 300, 400, 512, 600, 700, 850, 1024, 1400, 2048, 4096):
+            for stretch in (2, 3, 4, 5):
+                (steps, kernel, tx, _), _ = _plan(n, n, dtype, stretch, 0, force, perm, scheme)
+                assert steps == 1 or tx >= 16, (n, dtype, force, perm, scheme, stretch, kernel, tx)
+
+
+# grids in and beyond the caches whose launches of two (and, with a tensor, three
+# and four) steps have their tiles from few_steps
+FEW_GRIDS = [(523, 401), (1030, 777), (1337, 1411), (1901, 1803)]
+
+
+def test_the_few_step_grids_reach_each_tile():
+    reached = {_plan(nx, ny, dtype, d, 1, force, perm, scheme)[0][:2]
+               for nx, ny in FEW_GRIDS for dtype, force, perm, scheme in FORMS for d in (2, 3, 4)}
+    assert {(2, 0), (2, 1), (3, 1), (4, 1)} <= reached
