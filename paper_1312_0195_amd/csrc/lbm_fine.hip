@@ -1389,7 +1389,8 @@ struct StepDFn {
 // 6.70 and 3000 x 2000 39.0; now 2.73, 6.17 and 37.4 (other sizes within 2% or
 // faster; over 18 grids the plan is 0.6% off the best tile and depth tried, on
 // average, and was 2.5%).
-double launch_us(const lbm_params &p, bool force, int cus, int shape, int D, int tx, int ty)
+// A launch that cannot take less than `limit` is not summed up (infinity).
+double launch_us(const lbm_params &p, bool force, int cus, int shape, int D, int tx, int ty, double limit)
 {
     const bool f64 = p.pop_dtype == LBM_F64, fast = p.pop_dtype == LBM_F32_FAST;
     const double nt = (double)((p.nx + tx - 1) / tx) * ((p.ny + ty - 1) / ty);
@@ -1404,9 +1405,12 @@ double launch_us(const lbm_params &p, bool force, int cus, int shape, int D, int
     const double wave = fast ? 0.063 : p.scheme == LBM_SCHEME_GUO ? 0.185 : f64 ? 0.127 : lone ? 0.118 : 0.112;
     double t = r == 1.0 && rounds > 1.0 ? (lone ? 1.0 : 2.0) : 0.0;  // a lone tile waits for its own reads
     const double lat = r == 1.0 || full <= 1.0 ? 0.25 : 0.12;
-    for (int s = 0; s < D; ++s) t += std::max(0.42, lat + wave * r * ax * (ay - 2 * s) / 256.0);
     const double planes = 19.0 + (force ? 2.0 : 0.0) + (p.perm_kind == LBM_PERM_TENSOR ? 3.0 : 0.0);
-    return 2.7 + rounds * t + (double)p.nx * p.ny * planes * (f64 ? 8.0 : 4.0) / 8.0e6;
+    const double mem = (double)p.nx * p.ny * planes * (f64 ? 8.0 : 4.0) / 8.0e6;
+    const double least = D * std::max(0.42, lat + wave * r * ax * (ay - D + 1) / 256.0);  // of the sum below
+    if (2.7 + rounds * (t + least) + mem > limit * (1.0 + 1e-9)) return INFINITY;
+    for (int s = 0; s < D; ++s) t += std::max(0.42, lat + wave * r * ax * (ay - 2 * s) / 256.0);
+    return 2.7 + rounds * t + mem;
 }
 
 // Launches of few steps on grids that fill the device are bound by the state's
@@ -1456,20 +1460,29 @@ Plan plan_launches(const lbm_params &p, bool force, int cus)
 {
     Plan pl{};
     const bool f64 = p.pop_dtype == LBM_F64, fast = p.pop_dtype == LBM_F32_FAST;
+    int even[65] = {};  // the tile width of even columns of at most w cells
+    for (int w = 4; w <= 64; ++w) {
+        const int columns = (p.nx + w - 1) / w;
+        even[w] = (p.nx + columns - 1) / columns;
+    }
     for (int D = 2; D <= kMaxDepth; ++D) {
         Launch best{kTile1024, 1, 1, 1e30};
+        const int h2 = 2 * (D - 1);
+        // the large grids' tile first, as a limit for the others
+        double limit = 1e30;
+        if (D <= 10) limit = f64 ? launch_us(p, force, cus, kTile32, D, 32 - h2, 32 - h2, limit)
+                                 : launch_us(p, force, cus, kRows768, D, 64 - h2, 36 - h2, limit);
         auto offer = [&](int shape, int tx, int ty) {
-            const double us = launch_us(p, force, cus, shape, D, tx, ty);
+            const double us = launch_us(p, force, cus, shape, D, tx, ty, std::min(limit, best.us));
             if (us < best.us) best = Launch{shape, tx, ty, us};
         };
-        const int h2 = 2 * (D - 1);
         const int cap[3] = {512, 1024, 2048}, shape[3] = {kTile512, kTile1024, kTile2048};
         // rows of fewer than 16 cells read partial cache lines, which few steps do not
         // make up for (300^2, three steps: 6 x 75 tiles 6.3 us, 58 x 12 5.6)
         const int narrowest = D <= 5 && p.nx >= 64 && (double)p.nx * p.ny >= 40e3 ? 16 : 4;
         for (int i = 0; i < 3; ++i)
             for (int w = narrowest, last = 0; w <= 64 && w + h2 <= cap[i]; ++w) {
-                const int tx = (p.nx + (p.nx + w - 1) / w - 1) / ((p.nx + w - 1) / w);  // even columns of tiles
+                const int tx = even[w];
                 if (tx == last) continue;
                 last = tx;
                 const int room = cap[i] / (tx + h2) - h2;
